@@ -145,7 +145,8 @@ void build_moment_tiles(Plan &P)
 {
     P.tiles.clear();
     for (int c = 0; c < (int)P.cd.size(); c++) {
-        const int nt = moment_tiles(P.cd[c].nx, P.cd[c].ny, P.cd[c].nz);
+        const MomentTiles &m = P.cd[c].mom;
+        const int nt = m.ntx * m.nty * m.ntz;
         for (int t = 0; t < nt; t++) P.tiles.push_back(Tile{c, t});
     }
 }
@@ -289,6 +290,12 @@ std::string make_plan(const lbm_case *cases, const lbm_body *bodies, int n, cons
         P.maxL3 = std::max(P.maxL3, d.L * d.L * d.L);
         if (d.M > 0) P.max_slab = std::max(P.max_slab, d.dz * k.nx * k.ny);
         P.max_tiles += (d.cells + 63) / 64;
+    }
+    if (mom) {
+        moment_plan(P.cd.data(), n, moff > 0);
+        long long nt = 0;
+        for (const CaseDev &d : P.cd) nt += (long long)d.mom.ntx * d.mom.nty * d.mom.ntz;
+        P.max_tiles = std::max(P.max_tiles, nt);
     }
     if (mom)
         build_moment_tiles(P);
@@ -669,7 +676,8 @@ static int32_t do_lbm_step(lbm_ctx *ctx)
     const int src = ctx->cur, dst = 1 - ctx->cur;
     if (ctx->has_body) HIPCHK(ctx, hipEventRecord(ctx->fork, ctx->stream), "record fork event");
     if (ctx->opt.storage == LBM_MOM)
-        HIPCHK(ctx, launch_moment_step(ctx->pop[src], ctx->pop[dst], ctx->p, (int)ctx->plan.tiles.size(), ctx->stream),
+        HIPCHK(ctx, launch_moment_step(ctx->pop[src], ctx->pop[dst], ctx->p, (int)ctx->plan.tiles.size(),
+                                       ctx->plan.cd[0].mom.cap, ctx->stream),
                "lbm_step");
     else if (ctx->plan.q == 19)
         HIPCHK(ctx,

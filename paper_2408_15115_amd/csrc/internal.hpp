@@ -7,6 +7,13 @@
 
 namespace turret {
 
+// Column tiles of the moment-storage step: tiles of width x rows cells and
+// chunks of `planes` z planes, ntx x nty x ntz of them; rows <= cap, the row
+// capacity of the workgroup (the same for all cases of a context).
+struct MomentTiles {
+    int width, rows, planes, ntx, nty, ntz, cap;
+};
+
 // Static description of one case, in device memory.
 struct CaseDev {
     int nx, ny, nz;
@@ -24,6 +31,7 @@ struct CaseDev {
     double force_offset;    // 0: stress integral at the markers; > 0: on the parallel surface
     float uw_lo, uw_hi;     // x velocity of a no-slip bottom / top wall
     long long xreg_off;     // moment storage: cell offset of the case's expanded region (edge L + 2)
+    MomentTiles mom;        // moment storage: tiles of the step
     int LB[3];              // FP16/BF16 storage: edges of the case's full-precision box (0: none)
     long long fine_off;     // element offset of the case's box in each box buffer ([27][LBz][LBy][LBx])
 };
@@ -144,8 +152,8 @@ hipError_t launch_stream_collide19(const void *src, void *dst, const DevPtrs &p,
 // Moment storage (FP32): the z-marching step over the moment tile table, and
 // per-case conversions between moments (with the forcing shifts of the last
 // correction) and population deviations ([10][plane] <-> [27][plane]).
-int moment_tiles(int nx, int ny, int nz);
-hipError_t launch_moment_step(const void *src, void *dst, const DevPtrs &p, int ntiles, hipStream_t s);
+void moment_plan(CaseDev *cases, int n_cases, bool bodies);   // sets the tiles of all cases of a context
+hipError_t launch_moment_step(const void *src, void *dst, const DevPtrs &p, int ntiles, int cap, hipStream_t s);
 hipError_t launch_moments_expand(const float *src, float *dst, const DevPtrs &p, int c, hipStream_t s);
 // the same with the case's cell count from the host plan (no synchronizing read)
 hipError_t launch_moments_expand_n(const float *src, float *dst, const DevPtrs &p, int c, long long cells,

@@ -172,7 +172,7 @@ struct CodecMom {
 // (forcing shifts included) of every cell of the particle region and a
 // one-cell rim, edge E = L + 2, into rpop.  Rim planes beyond a z wall are
 // never pulled and are left alone.
-__global__ void k_region_expand_mom(const float *__restrict__ src, DevPtrs p)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) k_region_expand_mom(const float *__restrict__ src, DevPtrs p)
 {
     const int c = blockIdx.y;
     const CaseDev cd = p.cases[c];
@@ -241,7 +241,7 @@ __device__ inline void pull_region(const DevPtrs &p, const CaseDev &cd, int a, i
 // by k_markers (inside some tile's stencil box) are visited; the others are
 // read by no interpolation and carry no force.
 template <class CD>
-__global__ void k_region_gather(const typename CD::T *__restrict__ src, DevPtrs p, int sid)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) k_region_gather(const typename CD::T *__restrict__ src, DevPtrs p, int sid)
 {
     const int c = blockIdx.y;
     const CaseDev cd = p.cases[c];
@@ -527,7 +527,7 @@ __device__ inline TileBox mark_points(const DevPtrs &p, const CaseDev &cd, const
 // the position, normal and rigid velocity of marker first + j and checks the
 // z range; the tile's stencil box goes to the tile table, and the cells of
 // that box (and of the force-surface points' box) are marked for this step.
-__global__ void __launch_bounds__(64) k_markers(DevPtrs p, int n_mtiles)
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) k_markers(DevPtrs p, int n_mtiles)
 {
     const int tix = tile_of_block((int)blockIdx.x, n_mtiles);
     if (tix >= n_mtiles) return;
@@ -1526,11 +1526,7 @@ static hipError_t ibm_impl(const void *prev, void *cur, const DevPtrs &p, int n_
     // plain start with at most kHBufs cycles: each cycle's spread rides on
     // the pass before it (force + spread 1, update c + spread c + 1)
     static_assert(kHBufs == 4, "the launch below instantiates 1..4 accumulators");
-    // register budget of the tile passes: 8 waves per SIMD (they fit the
-    // slots the lattice kernel frees) for the population stores, whose
-    // coupling runs beside that kernel; the occupancy the LDS allows for the
-    // moment store
-    constexpr int W = std::is_same<CD, CodecMom>::value ? 1 : 8;
+    constexpr int W = 8;   // register budget of the tile passes
     const int fused = ibm_fused(warm_mode, cycles);
     hipLaunchKernelGGL(k_interp_force_tiles<W>, tile_grid, blk, kLdsForce, s, p, n_mtiles, fused);
     if (force_surface) hipLaunchKernelGGL(k_offset_force, tile_grid, blk, 0, s, p, n_mtiles);

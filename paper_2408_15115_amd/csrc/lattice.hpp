@@ -152,12 +152,12 @@ struct Macro {
     float P[3][3];
 };
 
-__device__ inline Macro macro(const Moments &m)
+// inv = 1 / (1 + m.r1)
+__device__ inline Macro macro(const Moments &m, float inv)
 {
     Macro o;
     o.r1 = m.r1;
     o.rho = 1.0f + m.r1;
-    float inv = 1.0f / o.rho;
 #pragma unroll
     for (int a = 0; a < 3; a++) o.u[a] = m.j[a] * inv;
     float iso = CS2 * m.r1;
@@ -169,6 +169,8 @@ __device__ inline Macro macro(const Moments &m)
     o.P[1][2] = o.P[2][1] = m.pyz - m.j[1] * o.u[2];
     return o;
 }
+
+__device__ inline Macro macro(const Moments &m) { return macro(m, 1.0f / (1.0f + m.r1)); }
 
 // u^k for k in {0,1,2} per axis
 struct Pow3 {

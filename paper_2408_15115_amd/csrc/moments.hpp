@@ -50,10 +50,17 @@ __device__ __forceinline__ void expand(const float m[10], const float sh[4], flo
     hermite_to_populations(A, out);
 }
 
+// 1 / v by the hardware's approximation and one Newton step (about 1 ulp).
+__device__ __forceinline__ float inverse(float v)
+{
+    const float r = __builtin_amdgcn_rcpf(v);
+    return fmaf(fmaf(-v, r, 1.0f), r, r);
+}
+
 // Collide: raw moments of the pulled deviations -> the stored post-collision state.
 __device__ __forceinline__ void collide_to_moments(const Moments &rm, float om, float m[10], bool &bad)
 {
-    const Macro M = macro(rm);
+    const Macro M = macro(rm, inverse(1.0f + rm.r1));
     const float u2 = M.u[0] * M.u[0] + M.u[1] * M.u[1] + M.u[2] * M.u[2];
     bad = !(fabsf(M.r1) < 1.0f) || !(u2 < 0.25f);
     m[0] = M.r1;
