@@ -1213,7 +1213,7 @@ int32_t lbm_log_read(lbm_ctx *ctx, int32_t c, double *out, int32_t max_records, 
 // ------------------------------------------------------- learned warm start
 static_assert(LBM_MLP_IN == kMlpIn && LBM_MLP_PARAMS == kMlpParams, "network sizes of the header");
 
-static size_t mlp_layout(int max_batch, size_t off[12])
+static size_t mlp_layout(int max_batch, size_t off[8])
 {
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -1221,19 +1221,15 @@ static size_t mlp_layout(int max_batch, size_t off[12])
         o = align256(o + std::max<size_t>(bytes, 1));
         return at;
     };
-    const size_t P = kMlpParams, n = (size_t)max_batch;
-    const size_t slices = (n + kMlpSlice - 1) / kMlpSlice, blocks = (n + 255) / 256;
-    off[0] = take(4 * P);                      // th32
-    off[1] = take(2 * P);                      // th16
-    off[2] = take(4 * P);                      // m
-    off[3] = take(4 * P);                      // v
-    off[4] = take(4 * P);                      // grad
-    off[5] = take(4);                          // loss
-    off[6] = take(4 * n * 4 * kMlpH);          // a1 a2 d1 d2
-    off[7] = take(4 * n * 2 * kMlpH);          // dz1 dz2
-    off[8] = take(4 * n * kMlpOut);            // dy
-    off[9] = take(4 * slices * P);             // gradient partials
-    off[10] = take(4 * blocks);                // loss partials
+    const size_t P = kMlpParams, parts = std::min<size_t>((size_t)max_batch, kMlpParts);
+    off[0] = take(4 * P);           // th32
+    off[1] = take(2 * P);           // th16
+    off[2] = take(4 * P);           // m
+    off[3] = take(4 * P);           // v
+    off[4] = take(4 * P);           // grad
+    off[5] = take(4);               // loss
+    off[6] = take(4 * parts * P);   // partial gradients
+    off[7] = take(4 * parts);       // partial losses
     return o;
 }
 
@@ -1243,7 +1239,7 @@ int32_t mlp_required_bytes(int32_t max_batch, int64_t *out_bytes)
         g_init_error = "mlp_required_bytes: max_batch must be 1..2^20";
         return LBM_EINVAL;
     }
-    size_t off[12];
+    size_t off[8];
     *out_bytes = (int64_t)mlp_layout(max_batch, off);
     return LBM_OK;
 }
@@ -1263,7 +1259,7 @@ int32_t mlp_create(void *dev_buf, int64_t bytes, int32_t max_batch, void *hip_st
         return LBM_ENOMEM;
     }
     lbm_mlp *m = new lbm_mlp();
-    size_t off[12];
+    size_t off[8];
     mlp_layout(max_batch, off);
     char *b = (char *)dev_buf;
     m->stream = (hipStream_t)hip_stream;
@@ -1274,18 +1270,8 @@ int32_t mlp_create(void *dev_buf, int64_t bytes, int32_t max_batch, void *hip_st
     m->v = (float *)(b + off[3]);
     m->grad = (float *)(b + off[4]);
     m->loss = (float *)(b + off[5]);
-    const size_t n = (size_t)max_batch;
-    float *act = (float *)(b + off[6]);
-    m->sc.a1 = act;
-    m->sc.a2 = act + n * kMlpH;
-    m->sc.d1 = act + 2 * n * kMlpH;
-    m->sc.d2 = act + 3 * n * kMlpH;
-    float *dz = (float *)(b + off[7]);
-    m->sc.dz1 = dz;
-    m->sc.dz2 = dz + n * kMlpH;
-    m->sc.dy = (float *)(b + off[8]);
-    m->sc.part = (float *)(b + off[9]);
-    m->sc.loss_part = (float *)(b + off[10]);
+    m->sc.part = (float *)(b + off[6]);
+    m->sc.loss_part = (float *)(b + off[7]);
     hipError_t e = hipMemsetAsync(dev_buf, 0, (size_t)need, m->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
     if (e != hipSuccess) {
@@ -1345,10 +1331,11 @@ int32_t mlp_grad(lbm_mlp *m, const float *dev_x, const float *dev_t, int32_t n, 
 
 int32_t mlp_train_step(lbm_mlp *m, const float *dev_x, const float *dev_t, int32_t n, float lr, float *dev_loss)
 {
-    int32_t r = mlp_grad(m, dev_x, dev_t, n, nullptr, dev_loss);
-    if (r) return r;
+    if (!m || !dev_x || !dev_t || n < 1 || n > m->max_batch)
+        return m ? mlp_fail(m, LBM_EINVAL, "mlp_train_step: bad arguments or n > max_batch") : LBM_EINVAL;
     m->step += 1;
-    hipError_t e = launch_mlp_adam(m->th32, m->th16, m->m, m->v, m->grad, lr, m->step, m->stream);
+    hipError_t e = launch_mlp_train_step(m->th32, m->th16, m->m, m->v, dev_x, dev_t, n, m->sc, lr, m->step,
+                                         dev_loss ? dev_loss : m->loss, m->stream);
     if (e != hipSuccess) return mlp_fail(m, LBM_EHIP, std::string("mlp_train_step: ") + hipGetErrorString(e));
     return LBM_OK;
 }

@@ -1,7 +1,7 @@
 // mlp.hip -- the warm-start network of the learned IBM form: a
 // 16 -> 64 -> 64 -> 3 multilayer perceptron with SiLU hidden activations,
 // FP16 weights and FP32 accumulation; inference for every marker, and
-// training (per-sample forward/backward, deterministic weight-gradient sums,
+// training (forward, backward and weight gradients in FP32 on the matrix cores,
 // Adam) on samples the solver produced.
 //
 // Parameter layout (flat): W1[64][16] b1[64] W2[64][64] b2[64] W3[3][64] b3[3].
@@ -14,54 +14,14 @@
 
 namespace turret {
 
-__device__ __forceinline__ float sigmoidf(float x) { return 1.0f / (1.0f + __expf(-x)); }
-// The same with the hardware reciprocal (about 1 ulp), for FP16-operand inference.
+// The logistic function with the hardware reciprocal (about 1 ulp), for
+// FP16-operand inference, and with one Newton step more for training.
 __device__ __forceinline__ float sigmoid_fast(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
-
-// Weights: FP16 in HBM, widened once per workgroup into LDS.
-__device__ __forceinline__ void load_weights(const _Float16 *__restrict__ th16, float *w)
+__device__ __forceinline__ float sigmoidf(float x)
 {
-    for (int i = threadIdx.x; i < kMlpParams; i += blockDim.x) w[i] = (float)th16[i];
-    __syncthreads();
-}
-
-// Forward pass of one sample; optionally keeps a1, a2, silu'(z1), silu'(z2).
-__device__ __forceinline__ void mlp_forward_one(const float *w, const float x[kMlpIn], float y[kMlpOut],
-                                                float *a1o, float *a2o, float *d1o, float *d2o, int stride)
-{
-    const float *W1 = w + kOffW1, *b1 = w + kOffB1, *W2 = w + kOffW2, *b2 = w + kOffB2, *W3 = w + kOffW3,
-                *b3 = w + kOffB3;
-    float a1[kMlpH];
-#pragma unroll
-    for (int o = 0; o < kMlpH; o++) {
-        float z = b1[o];
-#pragma unroll
-        for (int i = 0; i < kMlpIn; i++) z = fmaf(W1[o * kMlpIn + i], x[i], z);
-        const float s = sigmoidf(z);
-        a1[o] = z * s;
-        if (a1o) {
-            a1o[o * stride] = a1[o];
-            d1o[o * stride] = s + z * s * (1.0f - s);
-        }
-    }
-    float y0 = b3[0], y1 = b3[1], y2 = b3[2];
-    for (int o = 0; o < kMlpH; o++) {
-        float z = b2[o];
-#pragma unroll
-        for (int i = 0; i < kMlpH; i++) z = fmaf(W2[o * kMlpH + i], a1[i], z);
-        const float s = sigmoidf(z);
-        const float a = z * s;
-        if (a2o) {
-            a2o[o * stride] = a;
-            d2o[o * stride] = s + z * s * (1.0f - s);
-        }
-        y0 = fmaf(W3[o], a, y0);
-        y1 = fmaf(W3[kMlpH + o], a, y1);
-        y2 = fmaf(W3[2 * kMlpH + o], a, y2);
-    }
-    y[0] = y0;
-    y[1] = y1;
-    y[2] = y2;
+    const float v = 1.0f + __expf(-x), r = __builtin_amdgcn_rcpf(v);
+    const float t = fmaf(fmaf(-v, r, 1.0f), r, r);
+    return v > 3.0e38f ? 0.0f : t;   // (where exp overflows)
 }
 
 // ------------------------------------------------ inference on the matrix cores
@@ -330,141 +290,282 @@ __global__ void __launch_bounds__(256) k_mlp_warm_start(const _Float16 *__restri
     });
 }
 
-// Training, pass 1: forward of every sample, keeping the activations and
-// SiLU derivatives (scratch, layout [field][sample]), dY = (Y - T)/N and the
-// per-block loss partial 1/(2N) sum |Y - T|^2.
-__global__ void __launch_bounds__(256) k_mlp_fwd_train(const _Float16 *__restrict__ th16, const float *__restrict__ X,
-                                                       const float *__restrict__ Tg, int n, MlpScratch sc)
+// ------------------------------------------------------------- training
+// Forward, backward and the weight gradients in one pass, on
+// v_mfma_f32_16x16x4_f32: FP32 operands (the FP16 weights widened) and FP32
+// accumulation throughout.  A workgroup of 4 waves takes 64 samples at a time.
+// Each wave runs 16 of them, the columns of every product, through the layers
+// and back in registers: with step e of a 16-wide chunk taking input 4 g + e
+// in lanes 16 g .. 16 g + 15, the rows a lane holds of one product are the
+// operand it supplies to the next.  The weights are staged in LDS as operand
+// images (one 16-byte read per lane and four steps, no bank conflicts).  The
+// activations and errors then go to LDS, sample after sample in a row, and the
+// weight gradients are products over the 64 samples: wave w forms rows 16 w ..
+// 16 w + 15 of dW2 and dW1 and columns 16 w .. of dW3, kept in registers over
+// all samples of the workgroup.  Sums run in a fixed order throughout, so the
+// gradient is bitwise reproducible.
+//
+// Bound by latency (1.3 GFLOP at 8192 samples would take 10 us of the chip's
+// FP32 rate over five gradients): one gradient took 214 us in four passes of
+// one thread per sample or parameter through HBM scratch, and takes 17 us so
+// (13 for this kernel).
+typedef float row4_t __attribute__((ext_vector_type(4)));
+constexpr int kTrainSamples = 64;            // per workgroup and round
+constexpr int kTrainPitch = kTrainSamples + 4;   // floats per LDS row: 16-byte aligned, no bank conflicts
+
+struct TrainLds {
+    row4_t w1[kHChunks][64];                // [row tile][lane]: W1[16 t + i][4 g ..]
+    row4_t w2[kHChunks][kHChunks][64];      // [row tile][chunk][lane]: W2[16 t + i][16 c + 4 g ..]
+    row4_t w2t[kHChunks][kHChunks][64];     // the same of W2 transposed
+    row4_t w3[kHChunks][64];                // [chunk][lane]: W3[i][16 c + 4 g ..], rows past the outputs 0
+    float w3t[kMlpOut][kHChunks][64];       // [step][row tile][lane]: W3[e][16 t + i] for g = 0, else 0
+    float b1[kMlpH], b2[kMlpH], b3[4];
+    float x[kMlpIn][kTrainPitch], a1[kMlpH][kTrainPitch], a2[kMlpH][kTrainPitch];
+    float z1[kMlpH][kTrainPitch], z2[kMlpH][kTrainPitch], dy[16][kTrainPitch];
+    float loss[4];
+};
+static_assert(kMlpIn == 16 && kHChunks == 4, "one wave per 16 rows of the hidden layers, one chunk of inputs");
+
+__device__ __forceinline__ float4_t mfma4(const row4_t &a, const row4_t &b, float4_t c)
 {
-    __shared__ float w[kMlpParams];
-    __shared__ float red[256];
-    load_weights(th16, w);
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    float l = 0.0f;
-    if (s < n) {
-        float x[kMlpIn], y[kMlpOut];
 #pragma unroll
-        for (int i = 0; i < kMlpIn; i++) x[i] = X[(long long)s * kMlpIn + i];
-        mlp_forward_one(w, x, y, sc.a1 + s, sc.a2 + s, sc.d1 + s, sc.d2 + s, n);
+    for (int e = 0; e < 4; e++) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
+    return c;
+}
+
+__device__ inline void train_stage(const _Float16 *__restrict__ th, TrainLds &L)
+{
+    // four parameters per thread and round; all loads before the first store
+    constexpr int kVecs = (kMlpParams + 3) / 4, kRounds = (kVecs + 255) / 256;
+    half4_t v[kRounds];
 #pragma unroll
-        for (int j = 0; j < kMlpOut; j++) {
-            const float e = y[j] - Tg[(long long)s * kMlpOut + j];
-            sc.dy[j * n + s] = e / (float)n;
-            l += e * e;
+    for (int j = 0; j < kRounds; j++) v[j] = load_half4(th, 4 * std::min((int)threadIdx.x + 256 * j, kVecs - 1));
+    const row4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (threadIdx.x < 64)
+#pragma unroll
+        for (int c = 0; c < kHChunks; c++) {
+            if ((threadIdx.x & 15) >= kMlpOut) L.w3[c][threadIdx.x] = zero;
+            if (threadIdx.x >= 16)
+#pragma unroll
+                for (int e = 0; e < kMlpOut; e++) L.w3t[e][c][threadIdx.x] = 0.0f;
+        }
+    if (threadIdx.x == 64) L.b3[3] = 0.0f;
+    for (int k = threadIdx.x; k < (16 - kMlpOut) * kTrainPitch; k += 256) L.dy[kMlpOut + k / kTrainPitch][k % kTrainPitch] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kRounds; j++) {
+        const int p = 4 * ((int)threadIdx.x + 256 * j);
+        row4_t f;
+#pragma unroll
+        for (int e = 0; e < 4; e++) f[e] = (float)v[j][e];
+        if (p < kOffB1) {
+            const int o = p / kMlpIn, q = p % kMlpIn;
+            L.w1[o >> 4][(o & 15) + 16 * (q >> 2)] = f;
+        } else if (p < kOffW2) {
+#pragma unroll
+            for (int e = 0; e < 4; e++) L.b1[p - kOffB1 + e] = f[e];
+        } else if (p < kOffB2) {
+            const int o = (p - kOffW2) / kMlpH, q = (p - kOffW2) % kMlpH;
+            L.w2[o >> 4][q >> 4][(o & 15) + 16 * ((q & 15) >> 2)] = f;
+#pragma unroll
+            for (int e = 0; e < 4; e++) L.w2t[q >> 4][o >> 4][((q & 15) + e) + 16 * ((o & 15) >> 2)][o & 3] = f[e];
+        } else if (p < kOffW3) {
+#pragma unroll
+            for (int e = 0; e < 4; e++) L.b2[p - kOffB2 + e] = f[e];
+        } else if (p < kOffB3) {
+            const int o = (p - kOffW3) / kMlpH, q = (p - kOffW3) % kMlpH;
+            L.w3[q >> 4][o + 16 * ((q & 15) >> 2)] = f;
+#pragma unroll
+            for (int e = 0; e < 4; e++) L.w3t[o][q >> 4][(q & 15) + e] = f[e];
+        } else if (p < kMlpParams) {
+#pragma unroll
+            for (int e = 0; e < kMlpOut; e++) L.b3[e] = f[e];
         }
     }
-    red[threadIdx.x] = l;
     __syncthreads();
-    for (int st = blockDim.x / 2; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+}
+
+// SiLU of four pre-activations and its derivative.
+__device__ __forceinline__ void silu4(const float4_t &z, row4_t &a, row4_t &d)
+{
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+        const float s = sigmoidf(z[e]);
+        a[e] = z[e] * s;
+        d[e] = s + a[e] * (1.0f - s);
+    }
+}
+
+// Partial gradient and loss of the workgroup's samples into part[block] and
+// loss_part[block].
+__global__ void __launch_bounds__(256) k_mlp_train(const _Float16 *__restrict__ th16, const float *__restrict__ X,
+                                                   const float *__restrict__ Tg, int n, MlpScratch sc)
+{
+    __shared__ __align__(16) TrainLds L;
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+    const int col = 16 * w + i;   // this lane's sample of the round
+    train_stage(th16, L);
+    float4_t acc1 = {0.0f, 0.0f, 0.0f, 0.0f}, acc3 = acc1, acc2[kHChunks];
+#pragma unroll
+    for (int t = 0; t < kHChunks; t++) acc2[t] = acc1;
+    float sb1 = 0.0f, sb2 = 0.0f, sb3 = 0.0f, loss = 0.0f;
+    for (int base = kTrainSamples * blockIdx.x; base < n; base += kTrainSamples * gridDim.x) {
+        const int s = base + col;
+        const bool on = s < n;
+        row4_t x = {0.0f, 0.0f, 0.0f, 0.0f}, dy = x;
+        float tg[kMlpOut] = {};
+        if (on) {
+            x = *reinterpret_cast<const row4_t *>(X + (long long)s * kMlpIn + 4 * g);
+            if (g == 0)
+#pragma unroll
+                for (int e = 0; e < kMlpOut; e++) tg[e] = Tg[(long long)s * kMlpOut + e];
+        }
+        row4_t a1[kHChunks], d1[kHChunks], a2[kHChunks], d2[kHChunks];
+#pragma unroll
+        for (int t = 0; t < kHChunks; t++) {
+            const float *b = L.b1 + 16 * t + 4 * g;
+            const float4_t z = {b[0], b[1], b[2], b[3]};
+            silu4(mfma4(L.w1[t][l], x, z), a1[t], d1[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < kHChunks; t++) {
+            const float *b = L.b2 + 16 * t + 4 * g;
+            float4_t z = {b[0], b[1], b[2], b[3]};
+#pragma unroll
+            for (int c = 0; c < kHChunks; c++) z = mfma4(L.w2[t][c][l], a1[c], z);
+            silu4(z, a2[t], d2[t]);
+        }
+        float4_t y = {g == 0 ? L.b3[0] : 0.0f, g == 0 ? L.b3[1] : 0.0f, g == 0 ? L.b3[2] : 0.0f, 0.0f};
+#pragma unroll
+        for (int c = 0; c < kHChunks; c++) y = mfma4(L.w3[c][l], a2[c], y);
+        if (on && g == 0)
+#pragma unroll
+            for (int e = 0; e < kMlpOut; e++) {
+                const float r = y[e] - tg[e];
+                dy[e] = r / (float)n;
+                loss += r * r;
+            }
+        // back: dz2 = (W3^T dy) silu'(z2), dz1 = (W2^T dz2) silu'(z1)
+#pragma unroll
+        for (int t = 0; t < kHChunks; t++) {
+            float4_t z = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int e = 0; e < kMlpOut; e++) z = __builtin_amdgcn_mfma_f32_16x16x4f32(L.w3t[e][t][l], dy[e], z, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                d2[t][e] *= z[e];
+                L.z2[16 * t + 4 * g + e][col] = d2[t][e];
+                L.a1[16 * t + 4 * g + e][col] = a1[t][e];
+                L.a2[16 * t + 4 * g + e][col] = a2[t][e];
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < kHChunks; t++) {
+            float4_t z = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int c = 0; c < kHChunks; c++) z = mfma4(L.w2t[t][c][l], d2[c], z);
+#pragma unroll
+            for (int e = 0; e < 4; e++) L.z1[16 * t + 4 * g + e][col] = z[e] * d1[t][e];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; e++) L.x[4 * g + e][col] = x[e];
+        if (g == 0)
+#pragma unroll
+            for (int e = 0; e < kMlpOut; e++) L.dy[e][col] = dy[e];
         __syncthreads();
-    }
-    if (threadIdx.x == 0) sc.loss_part[blockIdx.x] = red[0] * 0.5f / (float)n;
-}
-
-// Training, pass 2: back-propagate dY to dz2 = (W3^T dY) silu'(z2) and
-// dz1 = (W2^T dz2) silu'(z1) per sample.
-__global__ void __launch_bounds__(256) k_mlp_bwd_train(const _Float16 *__restrict__ th16, int n, MlpScratch sc)
-{
-    __shared__ float w[kMlpParams];
-    load_weights(th16, w);
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    const float *W2 = w + kOffW2, *W3 = w + kOffW3;
-    const float dy0 = sc.dy[s], dy1 = sc.dy[n + s], dy2 = sc.dy[2 * n + s];
-    float dz2[kMlpH];
+        // the samples' part of the gradients
 #pragma unroll
-    for (int o = 0; o < kMlpH; o++) {
-        const float g = W3[o] * dy0 + W3[kMlpH + o] * dy1 + W3[2 * kMlpH + o] * dy2;
-        dz2[o] = g * sc.d2[o * n + s];
-        sc.dz2[o * n + s] = dz2[o];
-    }
-    for (int i = 0; i < kMlpH; i++) {
-        float g = 0.0f;
+        for (int q = 0; q < kTrainSamples / 16; q++) {
+            const int at = 16 * q + 4 * g;
+            auto row = [&](const float (*m)[kTrainPitch], int r) { return *reinterpret_cast<const row4_t *>(&m[r][at]); };
+            const row4_t z2 = row(L.z2, 16 * w + i), z1 = row(L.z1, 16 * w + i), d = row(L.dy, i);
 #pragma unroll
-        for (int o = 0; o < kMlpH; o++) g = fmaf(W2[o * kMlpH + i], dz2[o], g);
-        sc.dz1[i * n + s] = g * sc.d1[i * n + s];
+            for (int t = 0; t < kHChunks; t++) acc2[t] = mfma4(z2, row(L.a1, 16 * t + i), acc2[t]);
+            acc1 = mfma4(z1, row(L.x, i), acc1);
+            acc3 = mfma4(d, row(L.a2, 16 * w + i), acc3);
+            sb1 += (z1[0] + z1[1]) + (z1[2] + z1[3]);
+            sb2 += (z2[0] + z2[1]) + (z2[2] + z2[3]);
+            sb3 += (d[0] + d[1]) + (d[2] + d[3]);
+        }
+        __syncthreads();   // before the next round's stores
     }
+    float *part = sc.part + (long long)blockIdx.x * kMlpParams;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+        const int o = 16 * w + 4 * g + e;
+        part[kOffW1 + o * kMlpIn + i] = acc1[e];
+#pragma unroll
+        for (int t = 0; t < kHChunks; t++) part[kOffW2 + o * kMlpH + 16 * t + i] = acc2[t][e];
+        if (g == 0 && e < kMlpOut) part[kOffW3 + e * kMlpH + 16 * w + i] = acc3[e];
+    }
+    // bias gradients: the four lanes of a row each hold a quarter of its samples
+    auto quads = [&](float v) {
+        v += __shfl_xor(v, 16);
+        return v + __shfl_xor(v, 32);
+    };
+    sb1 = quads(sb1);
+    sb2 = quads(sb2);
+    sb3 = quads(sb3);
+    if (g == 0) {
+        part[kOffB1 + 16 * w + i] = sb1;
+        part[kOffB2 + 16 * w + i] = sb2;
+        if (w == 0 && i < kMlpOut) part[kOffB3 + i] = sb3;
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) loss += __shfl_xor(loss, o);
+    if (l == 0) L.loss[w] = loss;
+    __syncthreads();
+    if (threadIdx.x == 0) sc.loss_part[blockIdx.x] = ((L.loss[0] + L.loss[1]) + (L.loss[2] + L.loss[3])) * 0.5f / (float)n;
 }
 
-// Training, pass 3: weight gradients as sums over samples of outer products,
-// one thread per parameter per slice of samples (partial[slice][param]); the
-// sums over slices are taken in a fixed order by k_mlp_reduce, so the
-// gradient is bitwise reproducible.
-__global__ void __launch_bounds__(256) k_mlp_wgrad(const float *__restrict__ X, int n, int slice, MlpScratch sc)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= kMlpParams) return;
-    const int s0 = blockIdx.y * slice, s1 = min(n, s0 + slice);
-    const float *u = nullptr, *v = nullptr;   // gradient = sum_s u[s] * v[s]
-    int vstride = 0;
-    const float *vX = nullptr;
-    int xi = 0;
-    if (p < kOffB1) {                 // W1[o][i] = sum dz1[o] x[i]
-        const int o = p / kMlpIn;
-        xi = p - o * kMlpIn;
-        u = sc.dz1 + (long long)o * n;
-        vX = X;
-    } else if (p < kOffW2) {          // b1[o] = sum dz1[o]
-        u = sc.dz1 + (long long)(p - kOffB1) * n;
-    } else if (p < kOffB2) {          // W2[o][i] = sum dz2[o] a1[i]
-        const int q = p - kOffW2, o = q / kMlpH, i = q - o * kMlpH;
-        u = sc.dz2 + (long long)o * n;
-        v = sc.a1 + (long long)i * n;
-        vstride = 1;
-    } else if (p < kOffW3) {          // b2[o] = sum dz2[o]
-        u = sc.dz2 + (long long)(p - kOffB2) * n;
-    } else if (p < kOffB3) {          // W3[j][i] = sum dy[j] a2[i]
-        const int q = p - kOffW3, j = q / kMlpH, i = q - j * kMlpH;
-        u = sc.dy + (long long)j * n;
-        v = sc.a2 + (long long)i * n;
-        vstride = 1;
-    } else {                          // b3[j] = sum dy[j]
-        u = sc.dy + (long long)(p - kOffB3) * n;
-    }
-    float acc = 0.0f;
-    if (vX) {
-        for (int s = s0; s < s1; s++) acc = fmaf(u[s], vX[(long long)s * kMlpIn + xi], acc);
-    } else if (vstride) {
-        for (int s = s0; s < s1; s++) acc = fmaf(u[s], v[s], acc);
-    } else {
-        for (int s = s0; s < s1; s++) acc += u[s];
-    }
-    sc.part[(long long)blockIdx.y * kMlpParams + p] = acc;
-}
+// Adam (Kingma & Ba): FP32 master weights and moments, and the FP16 copy used
+// by the forward passes (round to nearest even).
+struct AdamState {
+    float *th32, *m, *v;
+    _Float16 *th16;
+    float lr, c1, c2;   // c = 1 - beta^step
+};
 
-__global__ void __launch_bounds__(256) k_mlp_reduce(int nslices, int nloss, MlpScratch sc, float *__restrict__ grad,
-                                                    float *__restrict__ loss)
+__device__ inline void adam_update(const AdamState &A, int p, float g)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < kMlpParams) {
-        float g = 0.0f;
-        for (int k = 0; k < nslices; k++) g += sc.part[(long long)k * kMlpParams + p];
-        grad[p] = g;
-    }
-    if (p == 0 && loss) {
-        float l = 0.0f;
-        for (int k = 0; k < nloss; k++) l += sc.loss_part[k];
-        *loss = l;
-    }
-}
-
-// Adam (Kingma & Ba): FP32 master weights and moments; the FP16 copy used by
-// the forward passes is refreshed (round to nearest even).
-__global__ void __launch_bounds__(256) k_mlp_adam(float *__restrict__ th32, _Float16 *__restrict__ th16,
-                                                  float *__restrict__ m, float *__restrict__ v,
-                                                  const float *__restrict__ g, float lr, float c1, float c2)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= kMlpParams) return;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float mm = b1 * m[p] + (1.0f - b1) * g[p];
-    const float vv = b2 * v[p] + (1.0f - b2) * g[p] * g[p];
-    m[p] = mm;
-    v[p] = vv;
-    const float t = th32[p] - lr * (mm / c1) / (sqrtf(vv / c2) + eps);
-    th32[p] = t;
-    th16[p] = (_Float16)t;
+    const float mm = b1 * A.m[p] + (1.0f - b1) * g;
+    const float vv = b2 * A.v[p] + (1.0f - b2) * g * g;
+    A.m[p] = mm;
+    A.v[p] = vv;
+    const float t = A.th32[p] - A.lr * (mm / A.c1) / (sqrtf(vv / A.c2) + eps);
+    A.th32[p] = t;
+    A.th16[p] = (_Float16)t;
+}
+
+// Gradient and loss from the workgroups' partial sums, and with ADAM the
+// update instead of the gradient.  64 parameters per workgroup, 16 threads
+// each: a serial sum over the partials was a chain of up to 256 loads.
+template <bool ADAM>
+__global__ void __launch_bounds__(1024) k_mlp_reduce(int nparts, MlpScratch sc, float *__restrict__ grad,
+                                                     float *__restrict__ loss, AdamState A)
+{
+    __shared__ float sum[16][64];
+    const int j = threadIdx.x & 63, k0 = threadIdx.x >> 6, p = blockIdx.x * 64 + j;
+    float g = 0.0f;
+    if (p < kMlpParams) {
+#pragma unroll 4
+        for (int k = k0; k < nparts; k += 16) g += sc.part[(long long)k * kMlpParams + p];
+    }
+    sum[k0][j] = g;
+    __syncthreads();
+    if (k0 == 0 && p < kMlpParams) {
+#pragma unroll
+        for (int k = 1; k < 16; k++) g += sum[k][j];
+        if constexpr (ADAM) adam_update(A, p, g);
+        else grad[p] = g;
+    }
+    if (blockIdx.x == 0 && k0 == 1 && loss) {
+        float v = 0.0f;
+        for (int k = j; k < nparts; k += 64) v += sc.loss_part[k];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+        if (j == 0) *loss = v;
+    }
 }
 
 __global__ void k_mlp_round(const float *__restrict__ th32, _Float16 *__restrict__ th16)
@@ -498,23 +599,26 @@ hipError_t launch_mlp_warm_start(const _Float16 *th16, const DevPtrs &p, int Mto
     return hipGetLastError();
 }
 
+// Workgroups of the training pass: one per 64 samples up to one per CU, which
+// then take several rounds.
+static int train_blocks(int n) { return std::min((n + kTrainSamples - 1) / kTrainSamples, kMlpParts); }
+
 hipError_t launch_mlp_grad(const _Float16 *th16, const float *X, const float *Tg, int n, const MlpScratch &sc,
                            float *grad, float *loss, hipStream_t s)
 {
-    const int nb = (n + 255) / 256;
-    hipLaunchKernelGGL(k_mlp_fwd_train, dim3(nb), dim3(256), 0, s, th16, X, Tg, n, sc);
-    hipLaunchKernelGGL(k_mlp_bwd_train, dim3(nb), dim3(256), 0, s, th16, n, sc);
-    const int slices = (n + kMlpSlice - 1) / kMlpSlice;
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((kMlpParams + 255) / 256, slices), dim3(256), 0, s, X, n, kMlpSlice, sc);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((kMlpParams + 255) / 256), dim3(256), 0, s, slices, nb, sc, grad, loss);
+    const int nb = train_blocks(n);
+    hipLaunchKernelGGL(k_mlp_train, dim3(nb), dim3(256), 0, s, th16, X, Tg, n, sc);
+    hipLaunchKernelGGL(k_mlp_reduce<false>, dim3((kMlpParams + 63) / 64), dim3(1024), 0, s, nb, sc, grad, loss, AdamState{});
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_adam(float *th32, _Float16 *th16, float *m, float *v, const float *g, float lr, int step,
-                           hipStream_t s)
+hipError_t launch_mlp_train_step(float *th32, _Float16 *th16, float *m, float *v, const float *X, const float *Tg, int n,
+                                 const MlpScratch &sc, float lr, int step, float *loss, hipStream_t s)
 {
-    const float c1 = 1.0f - powf(0.9f, (float)step), c2 = 1.0f - powf(0.999f, (float)step);
-    hipLaunchKernelGGL(k_mlp_adam, dim3((kMlpParams + 255) / 256), dim3(256), 0, s, th32, th16, m, v, g, lr, c1, c2);
+    const int nb = train_blocks(n);
+    const AdamState A{th32, m, v, th16, lr, 1.0f - powf(0.9f, (float)step), 1.0f - powf(0.999f, (float)step)};
+    hipLaunchKernelGGL(k_mlp_train, dim3(nb), dim3(256), 0, s, th16, X, Tg, n, sc);
+    hipLaunchKernelGGL(k_mlp_reduce<true>, dim3((kMlpParams + 63) / 64), dim3(1024), 0, s, nb, sc, nullptr, loss, A);
     return hipGetLastError();
 }
 

@@ -13,7 +13,7 @@ constexpr int kOffB2 = kOffW2 + kMlpH * kMlpH;
 constexpr int kOffW3 = kOffB2 + kMlpH;
 constexpr int kOffB3 = kOffW3 + kMlpOut * kMlpH;
 constexpr int kMlpParams = kOffB3 + kMlpOut;   // 5443
-constexpr int kMlpSlice = 256;                 // samples per weight-gradient partial sum
+constexpr int kMlpParts = 256;                 // most partial gradients of a batch (workgroups of the training pass)
 
 // Warm-start features of marker k, each a 3-vector over the marker's scale
 // s_k = |h0(t)| + |h(t-1)|: the plain start h0(t) = U - I[u*], the previous
@@ -25,13 +25,10 @@ constexpr int kMlpSlice = 256;                 // samples per weight-gradient pa
 // s_k.
 constexpr int kFeatH0 = 0, kFeatHPrev = 3, kFeatDH = 6, kFeatDH0 = 9, kFeatNormal = 12, kFeatArea = 15;
 
-// Per-sample training scratch, [field][sample] layout (n samples).
+// Training scratch.
 struct MlpScratch {
-    float *a1, *a2, *d1, *d2;   // activations and SiLU derivatives, 64 fields each
-    float *dz1, *dz2;           // back-propagated pre-activation gradients, 64 fields each
-    float *dy;                  // output errors / n, 3 fields
-    float *part;                // weight-gradient partial sums [slices][params]
-    float *loss_part;           // loss partial sums per block
+    float *part;        // partial gradients [kMlpParts][kMlpParams]
+    float *loss_part;   // partial losses [kMlpParts]
 };
 
 struct DevPtrs;
@@ -39,8 +36,9 @@ hipError_t launch_mlp_forward(const _Float16 *th16, const float *X, int n, float
 hipError_t launch_mlp_warm_start(const _Float16 *th16, const DevPtrs &p, int Mtot, hipStream_t s);
 hipError_t launch_mlp_grad(const _Float16 *th16, const float *X, const float *T, int n, const MlpScratch &sc,
                            float *grad, float *loss, hipStream_t s);
-hipError_t launch_mlp_adam(float *th32, _Float16 *th16, float *m, float *v, const float *g, float lr, int step,
-                           hipStream_t s);
+// Gradient and one Adam step (step counts from 1); the loss before the step.
+hipError_t launch_mlp_train_step(float *th32, _Float16 *th16, float *m, float *v, const float *X, const float *T, int n,
+                                 const MlpScratch &sc, float lr, int step, float *loss, hipStream_t s);
 hipError_t launch_mlp_round(const float *th32, _Float16 *th16, hipStream_t s);
 
 }  // namespace turret
