@@ -81,10 +81,10 @@ struct CodecBF16 {
     }
     template <int I> __device__ static inline T enc(float g)
     {
-        uint32_t u = __float_as_uint(g * (float)store_scale(I));
-        if ((u & 0x7fffffffu) > 0x7f800000u) return (T)((u >> 16) | 0x40u);   // keep NaN a NaN
-        u += 0x7fffu + ((u >> 16) & 1u);                                        // round to nearest even
-        return (T)(u >> 16);
+        // v_cvt_pk_bf16_f32: round to nearest even, NaN stays NaN (one
+        // instruction for the five of the rounding in integers, which held
+        // the kernel at 4.77 TB/s where the FP16 store reaches 5.17)
+        return __builtin_bit_cast(T, (__bf16)(g * (float)store_scale(I)));
     }
 };
 
