@@ -44,6 +44,7 @@ struct Plan {
     long long fine_elems = 0;   // FP16/BF16 storage: floats of all full-precision boxes (per buffer)
     long long max_box = 0;      // cells of the largest box
     int block = 256;
+    int keep = 0;   // the lattice kernel's stores are ordinary ones (see store_policy)
 };
 
 std::string check_case(const lbm_case &c, const lbm_body *b)
@@ -149,6 +150,30 @@ void build_moment_tiles(Plan &P)
         const int nt = m.ntx * m.nty * m.ntz;
         for (int t = 0; t < nt; t++) P.tiles.push_back(Tile{c, t});
     }
+}
+
+// How the lattice kernels store a step's result.  It is next read a step
+// later, so the stores carry the non-temporal hint, with two exceptions
+// (measured, one step of the lattice kernel alone):
+//   - both population buffers together fit the 256 MB memory-side cache: the
+//     hint sends the data past it.  FP32, 131 x 77 x 93: 47 us with the hint,
+//     36 without; 104^3 (242 MB): 47 and 41; 110^3 (288 MB): 55 and 57.  With
+//     2-byte elements the two are within 5 % up to there, either way, so that
+//     form keeps the hint; moment storage below 64 MB too (64^3: 13.8 and 14.4;
+//     112^3: 41 and 36);
+//   - moment storage, whose step writes row by row, in boxes whose rows are
+//     not whole 64-cell wavefronts: the hint writes the lines that two rows
+//     share in parts.  160 x 160 x 480: 308 and 244 us; 250 x 250 x 760: 1233
+//     and 1008; 256 x 256 x 400: 489 and 501.
+void store_policy(Plan &P, int storage)
+{
+    constexpr long long kCache = 256LL << 20;
+    const long long bytes = 2 * P.pop_elems * elem_bytes(storage);
+    // moment storage: whichever holds for more of the context's cells
+    long long whole = 0, ragged = 0;
+    for (const CaseDev &d : P.cd) (d.nx % 64 != 0 ? ragged : whole) += d.cells;
+    P.keep = storage == LBM_MOM ? bytes >= kCache / 4 && (bytes <= kCache || ragged > whole)
+                                : storage == LBM_F32 && bytes <= kCache;
 }
 
 // Marker order and tiles of one case: sort the markers along a Morton curve
@@ -302,6 +327,7 @@ std::string make_plan(const lbm_case *cases, const lbm_body *bodies, int n, cons
     else
         build_tiles(P, P.block, opt ? opt->tile_order : 0);
     P.pop_elems = pop;
+    store_policy(P, opt ? opt->storage : LBM_F32);
     P.reg_cells = reg;
     P.Mtot = moff;
     size_t o = 0;
@@ -677,18 +703,18 @@ static int32_t do_lbm_step(lbm_ctx *ctx)
     if (ctx->has_body) HIPCHK(ctx, hipEventRecord(ctx->fork, ctx->stream), "record fork event");
     if (ctx->opt.storage == LBM_MOM)
         HIPCHK(ctx, launch_moment_step(ctx->pop[src], ctx->pop[dst], ctx->p, (int)ctx->plan.tiles.size(),
-                                       ctx->plan.cd[0].mom.cap, ctx->stream),
+                                       ctx->plan.cd[0].mom.cap, ctx->plan.keep, ctx->stream),
                "lbm_step");
     else if (ctx->plan.q == 19)
         HIPCHK(ctx,
                launch_stream_collide19(ctx->pop[src], ctx->pop[dst], ctx->p, (int)ctx->plan.tiles.size(),
-                                       ctx->opt.block, ctx->opt.collision, ctx->stream),
+                                       ctx->opt.block, ctx->opt.collision, ctx->plan.keep, ctx->stream),
                "lbm_step");
     else
         HIPCHK(ctx,
                launch_stream_collide(ctx->opt.storage, ctx->pop[src], ctx->pop[dst], ctx->p,
                                      (int)ctx->plan.tiles.size(), ctx->opt.block, ctx->opt.schedule,
-                                     ctx->opt.persist_wgs, ctx->opt.collision, ctx->stream),
+                                     ctx->opt.persist_wgs, ctx->opt.collision, ctx->plan.keep, ctx->stream),
                "lbm_step");
     if (ctx->plan.max_box > 0) {
         // the lattice kernel leaves the box cells to this step, which reads

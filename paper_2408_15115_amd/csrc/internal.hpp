@@ -143,17 +143,19 @@ constexpr int kLogCap = 1024;
 constexpr int kLogFields = 32;
 
 // ---------------------------------------------------------------- launchers
+// keep: store the result with ordinary stores, not non-temporal ones (FP32;
+// the caller's rule says when)
 // collision: 0 = recursive regularized, 1 = BGK (comparison; plain schedule)
 hipError_t launch_stream_collide(int storage, const void *src, void *dst, const DevPtrs &p, int ntiles,
-                                 int block, int schedule, int persist_wgs, int collision, hipStream_t s);
+                                 int block, int schedule, int persist_wgs, int collision, int keep, hipStream_t s);
 // The D3Q19 comparison lattice (fluid only, FP32, periodic, plain schedule).
 hipError_t launch_stream_collide19(const void *src, void *dst, const DevPtrs &p, int ntiles, int block,
-                                   int collision, hipStream_t s);
+                                   int collision, int keep, hipStream_t s);
 // Moment storage (FP32): the z-marching step over the moment tile table, and
 // per-case conversions between moments (with the forcing shifts of the last
 // correction) and population deviations ([10][plane] <-> [27][plane]).
 void moment_plan(CaseDev *cases, int n_cases, bool bodies);   // sets the tiles of all cases of a context
-hipError_t launch_moment_step(const void *src, void *dst, const DevPtrs &p, int ntiles, int cap, hipStream_t s);
+hipError_t launch_moment_step(const void *src, void *dst, const DevPtrs &p, int ntiles, int cap, int keep, hipStream_t s);
 hipError_t launch_moments_expand(const float *src, float *dst, const DevPtrs &p, int c, hipStream_t s);
 // the same with the case's cell count from the host plan (no synchronizing read)
 hipError_t launch_moments_expand_n(const float *src, float *dst, const DevPtrs &p, int c, long long cells,

@@ -68,7 +68,7 @@ __device__ __forceinline__ float from_right(float v, float edge)
     return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x130, 0xf, 0xf, false));
 }
 
-constexpr int kNonTemporal = 2;   // cache policy bit of the buffer stores
+constexpr int kRegular = 0, kNonTemporal = 2;   // cache policies of the buffer stores
 
 // The workgroup's LDS is all that a barrier of the step orders: global loads
 // in flight (the next plane's moments) stay in flight.
@@ -176,9 +176,9 @@ __device__ __forceinline__ void to_populations(float a0, float a1, float a2, flo
 }  // namespace mom
 
 namespace mom {
-template <int MY>
+template <int MY, int POLICY>
 struct Exchange {
-    static constexpr int kRows = MY;
+    static constexpr int kRows = MY, kPolicy = POLICY;   // (the form of the march goes with its LDS)
     float edge[2][2][MY + 2][12];      // the side wave's T into the tile: [plane parity][side][row][9 of 12]
     float up[2][9][MY + 1][MX];    // row r - 1's +1 populations for row r: [plane parity][value][r][x]
     float down[2][9][MY + 1][MX];  // row r + 1's -1 populations for row r: [plane parity][value][r + 1][x]
@@ -343,7 +343,7 @@ __device__ __forceinline__ void row_march(const Tiling &t, Lds &lds, BodyDev &bo
             __builtin_amdgcn_raw_buffer_store_b32(
                 __float_as_uint(mo[c]),
                 __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(oc.at) + c * t.plane, 0, (int)slab_bytes, 0x00027000),
-                (int)off, 0, kNonTemporal);
+                (int)off, 0, Lds::kPolicy);
     };
     LoadAhead ahead(t);
     // (the dropped stores: the loop is then entered, as it is repeated, with
@@ -520,12 +520,12 @@ __device__ __forceinline__ void march(const Tiling &t, Lds &lds, BodyDev &body)
 // own opposite z direction, already moved along x and y; no-slip and constant
 // pressure, the cell's own opposite direction, unmoved (no-slip plus the
 // moving wall's momentum, constant pressure with the sign reversed).
-template <int MY>
+template <int MY, int POLICY>
 __global__ void __launch_bounds__(64 * (MY + 3)) k_moment_step(const float *__restrict__ src, float *__restrict__ dst,
                                                                DevPtrs p, int ntiles)
 {
     using namespace mom;
-    __shared__ Exchange<MY> lds;
+    __shared__ Exchange<MY, POLICY> lds;
     const int b = blockIdx.x;
     const int ti = (b & 7) * ((ntiles + 7) >> 3) + (b >> 3);
     if (ti >= ntiles) return;
@@ -656,15 +656,21 @@ void moment_plan(CaseDev *cd, int n, bool bodies)
     for (int c = 0; c < n; c++) cd[c].mom = moment_tiling(cd[c].nx, cd[c].ny, cd[c].nz, cap, planes);
 }
 
-hipError_t launch_moment_step(const void *src, void *dst, const DevPtrs &p, int ntiles, int cap, hipStream_t s)
+hipError_t launch_moment_step(const void *src, void *dst, const DevPtrs &p, int ntiles, int cap, int keep, hipStream_t s)
 {
-    const int grid = (ntiles + 7) / 8 * 8;
-    if (cap == mom::kRowsLarge)
-        hipLaunchKernelGGL(k_moment_step<mom::kRowsLarge>, dim3(grid), dim3(64 * (mom::kRowsLarge + 3)), 0, s,
-                           (const float *)src, (float *)dst, p, ntiles);
-    else
-        hipLaunchKernelGGL(k_moment_step<mom::kRowsSmall>, dim3(grid), dim3(64 * (mom::kRowsSmall + 3)), 0, s,
-                           (const float *)src, (float *)dst, p, ntiles);
+    const dim3 grid((ntiles + 7) / 8 * 8);
+    const float *a = (const float *)src;
+    float *b = (float *)dst;
+    auto launch = [&](auto rows, auto policy) {
+        constexpr int MY = decltype(rows)::value, POLICY = decltype(policy)::value;
+        hipLaunchKernelGGL((k_moment_step<MY, POLICY>), grid, dim3(64 * (MY + 3)), 0, s, a, b, p, ntiles);
+    };
+    const std::integral_constant<int, mom::kRowsLarge> large;
+    const std::integral_constant<int, mom::kRowsSmall> small;
+    const std::integral_constant<int, mom::kRegular> regular;
+    const std::integral_constant<int, mom::kNonTemporal> streamed;
+    if (cap == mom::kRowsLarge) keep ? launch(large, regular) : launch(large, streamed);
+    else keep ? launch(small, regular) : launch(small, streamed);
     return hipGetLastError();
 }
 

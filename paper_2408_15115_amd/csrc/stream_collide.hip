@@ -13,13 +13,15 @@ namespace turret {
 
 // Every population is written once per step and not read again before the
 // next step: the stores carry the non-temporal hint (measured faster; the
-// same hint on the loads is not).
-template <class CD>
+// same hint on the loads is not), unless the context's two FP32 buffers stay
+// in the memory-side cache (KEEP).
+template <class CD, bool KEEP>
 __device__ __forceinline__ void store_all(typename CD::T *__restrict__ dst, long long plane, int off, const float out[Q])
 {
     Unroll<0, Q>::run([&](auto I) {
         constexpr int i = decltype(I)::value;
-        __builtin_nontemporal_store(CD::template enc<i>(out[i]), &dst[(long long)i * plane + off]);
+        if constexpr (KEEP) dst[(long long)i * plane + off] = CD::template enc<i>(out[i]);
+        else __builtin_nontemporal_store(CD::template enc<i>(out[i]), &dst[(long long)i * plane + off]);
     });
 }
 
@@ -29,7 +31,7 @@ __device__ __forceinline__ void store_all(typename CD::T *__restrict__ dst, long
 // flags non-finite density or |u| > 0.5 (bit 4) with one atomic per wave.
 // COLL 0: recursive-regularized collision (App. A); COLL 1: BGK for
 // comparison, f0 + (1 - 1/tau)(f - f0) with the raw off-equilibrium.
-template <class CD, int COLL>
+template <class CD, int COLL, bool KEEP>
 __device__ __forceinline__ void stream_collide_tile(const typename CD::T *__restrict__ src, typename CD::T *__restrict__ dst,
                                                     const CaseDev *__restrict__ cases, BodyDev *__restrict__ body, Tile tl,
                                                     int off)
@@ -81,7 +83,7 @@ __device__ __forceinline__ void stream_collide_tile(const typename CD::T *__rest
     if (in_box) return;
     int zc = z + z0;
     if (zc >= nz) zc -= nz;
-    store_all<CD>(dst + cd.pop_off, cd.plane, (zc * ny + y) * nx + x, out);
+    store_all<CD, KEEP>(dst + cd.pop_off, cd.plane, (zc * ny + y) * nx + x, out);
 }
 
 // SCHED 0: tile = workgroup; 1: XCD-grouped tiles (workgroups go
@@ -103,7 +105,7 @@ __device__ __forceinline__ void stream_collide_tile(const typename CD::T *__rest
 // schedules free of the loops.
 constexpr int kQueueChunk = 4;
 
-template <class CD, int SCHED, int COLL = 0>
+template <class CD, int SCHED, int COLL = 0, bool KEEP = false>
 __global__ void __launch_bounds__(256) k_stream_collide(const typename CD::T *__restrict__ src,
                                                         typename CD::T *__restrict__ dst,
                                                         const CaseDev *__restrict__ cases, BodyDev *__restrict__ body,
@@ -123,7 +125,7 @@ __global__ void __launch_bounds__(256) k_stream_collide(const typename CD::T *__
                 __syncthreads();
                 if (t0 >= hi) break;
                 const int t1 = min(t0 + kQueueChunk, hi);
-                for (int t = t0; t < t1; t++) stream_collide_tile<CD, COLL>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
+                for (int t = t0; t < t1; t++) stream_collide_tile<CD, COLL, KEEP>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
             }
         }
     } else if constexpr (SCHED == 4) {
@@ -138,15 +140,15 @@ __global__ void __launch_bounds__(256) k_stream_collide(const typename CD::T *__
                 __syncthreads();
                 if (chunk >= nchunks) break;
                 const int t0 = chunk * kQueueChunk, t1 = min(t0 + kQueueChunk, ntiles);
-                for (int t = t0; t < t1; t++) stream_collide_tile<CD, COLL>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
+                for (int t = t0; t < t1; t++) stream_collide_tile<CD, COLL, KEEP>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
             }
         }
     } else if constexpr (SCHED == 2) {
-        for (int t = blockIdx.x; t < ntiles; t += gridDim.x) stream_collide_tile<CD, COLL>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
+        for (int t = blockIdx.x; t < ntiles; t += gridDim.x) stream_collide_tile<CD, COLL, KEEP>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
     } else {
         int t = blockIdx.x;
         if constexpr (SCHED == 1) t = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-        if (t < ntiles) stream_collide_tile<CD, COLL>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
+        if (t < ntiles) stream_collide_tile<CD, COLL, KEEP>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
     }
 }
 
@@ -176,7 +178,7 @@ hipError_t launch_copy(void *dst, const void *src, long long bytes, hipStream_t 
 // --------------------------------------------------------------- launchers
 template <class CD>
 static hipError_t stream_collide_impl(const void *src, void *dst, const DevPtrs &p, int ntiles, int block,
-                                      int schedule, int persist_wgs, int collision, hipStream_t s)
+                                      int schedule, int persist_wgs, int collision, int keep, hipStream_t s)
 {
     using T = typename CD::T;
     if (collision == 1) {   // the comparison collision runs with the plain schedule only
@@ -209,6 +211,12 @@ static hipError_t stream_collide_impl(const void *src, void *dst, const DevPtrs 
                            ntiles, p.counter);
         break;
     default:
+        if constexpr (std::is_same<CD, CodecF32>::value)
+            if (keep) {
+                hipLaunchKernelGGL((k_stream_collide<CD, 0, 0, true>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body,
+                                   p.tiles, ntiles, p.counter);
+                break;
+            }
         hipLaunchKernelGGL((k_stream_collide<CD, 0>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles,
                            ntiles, p.counter);
     }
@@ -216,15 +224,15 @@ static hipError_t stream_collide_impl(const void *src, void *dst, const DevPtrs 
 }
 
 hipError_t launch_stream_collide(int storage, const void *src, void *dst, const DevPtrs &p, int ntiles,
-                                 int block, int schedule, int persist_wgs, int collision, hipStream_t s)
+                                 int block, int schedule, int persist_wgs, int collision, int keep, hipStream_t s)
 {
     switch (storage) {
     case ST_F16:
-        return stream_collide_impl<CodecF16>(src, dst, p, ntiles, block, schedule, persist_wgs, collision, s);
+        return stream_collide_impl<CodecF16>(src, dst, p, ntiles, block, schedule, persist_wgs, collision, keep, s);
     case ST_BF16:
-        return stream_collide_impl<CodecBF16>(src, dst, p, ntiles, block, schedule, persist_wgs, collision, s);
+        return stream_collide_impl<CodecBF16>(src, dst, p, ntiles, block, schedule, persist_wgs, collision, keep, s);
     default:
-        return stream_collide_impl<CodecF32>(src, dst, p, ntiles, block, schedule, persist_wgs, collision, s);
+        return stream_collide_impl<CodecF32>(src, dst, p, ntiles, block, schedule, persist_wgs, collision, keep, s);
     }
 }
 

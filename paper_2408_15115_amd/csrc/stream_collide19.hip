@@ -61,7 +61,7 @@ __device__ __forceinline__ int wrap(int v, int n)
 //      alone (om = 0), then out = geq + om (g - geq).
 // The moments on S and D, (a_1 + a_2) / (2 cs^6) and (a_1 - a_2) / (6 cs^6),
 // recombine on H_1 and H_2 as k1 = 18 a_1 + 9 a_2, k2 = 9 a_1 + 18 a_2.
-template <int COLL>
+template <int COLL, bool KEEP>
 __global__ void __launch_bounds__(256) k_stream_collide19(const float *__restrict__ src, float *__restrict__ dst,
                                                           const CaseDev *__restrict__ cases, BodyDev *__restrict__ body,
                                                           const Tile *__restrict__ tiles)
@@ -174,18 +174,18 @@ __global__ void __launch_bounds__(256) k_stream_collide19(const float *__restric
     }
     float *d = dst + cd.pop_off + (rowc + y) * nx + x;
 #pragma unroll
-    for (int i = 0; i < N; i++) __builtin_nontemporal_store(out[i], &d[(long long)i * plane]);
+    for (int i = 0; i < N; i++) {
+        if constexpr (KEEP) d[(long long)i * plane] = out[i];
+        else __builtin_nontemporal_store(out[i], &d[(long long)i * plane]);
+    }
 }
 
 hipError_t launch_stream_collide19(const void *src, void *dst, const DevPtrs &p, int ntiles, int block,
-                                   int collision, hipStream_t s)
+                                   int collision, int keep, hipStream_t s)
 {
-    if (collision == 1)
-        hipLaunchKernelGGL(k_stream_collide19<1>, dim3(ntiles), dim3(block), 0, s, (const float *)src, (float *)dst,
-                           p.cases, p.body, p.tiles);
-    else
-        hipLaunchKernelGGL(k_stream_collide19<0>, dim3(ntiles), dim3(block), 0, s, (const float *)src, (float *)dst,
-                           p.cases, p.body, p.tiles);
+    auto *kernel = collision == 1 ? (keep ? k_stream_collide19<1, true> : k_stream_collide19<1, false>)
+                                  : (keep ? k_stream_collide19<0, true> : k_stream_collide19<0, false>);
+    hipLaunchKernelGGL(kernel, dim3(ntiles), dim3(block), 0, s, (const float *)src, (float *)dst, p.cases, p.body, p.tiles);
     return hipGetLastError();
 }
 
