@@ -39,7 +39,7 @@ struct Plan {
     long long pop_elems = 0, reg_cells = 0;
     size_t off_cases, off_body, off_tiles, off_counter, off_mcase, off_xb, off_nb, off_dS, off_X, off_N, off_U, off_hk,
         off_dh, off_part, off_res, off_reg, off_H, off_feat, off_h0, off_hk2, off_hs, off_dSo, off_mtiles, off_tbox, off_log,
-        off_mark, off_wt, off_dsh, off_rpop, off_fine0, off_fine1, aux_bytes;
+        off_mark, off_mark2, off_xmark, off_wt, off_dsh, off_rpop, off_fine0, off_fine1, aux_bytes;
     long long xreg_cells = 0;   // moment storage: cells of all expanded regions (edge L + 2)
     long long fine_elems = 0;   // FP16/BF16 storage: floats of all full-precision boxes (per buffer)
     long long max_box = 0;      // cells of the largest box
@@ -356,6 +356,8 @@ std::string make_plan(const lbm_case *cases, const lbm_body *bodies, int n, cons
     P.off_reg = take(sizeof(float) * kRegFields * std::max<long long>(reg, 1));
     P.off_H = take(sizeof(long long) * 3 * kHBufs * std::max<long long>(reg, 1));
     P.off_mark = take((size_t)std::max<long long>(reg, 1));
+    P.off_mark2 = take((size_t)std::max<long long>(reg, 1));
+    P.off_xmark = take((size_t)std::max<long long>(mom ? P.xreg_cells : 0, 1));
     P.off_feat = take(sizeof(float) * kMlpIn * M);
     P.off_h0 = take(sizeof(double) * 3 * M);
     P.off_hk2 = take(sizeof(double) * 3 * M);
@@ -594,6 +596,8 @@ int32_t lbm_init(const lbm_case *cases, const lbm_body *bodies, int32_t n_cases,
     p.H = (long long *)(a + P.off_H);
     p.hstride = 3 * std::max<long long>(P.reg_cells, 1);
     p.mark = (unsigned char *)(a + P.off_mark);
+    p.mark2 = (unsigned char *)(a + P.off_mark2);
+    p.xmark = ctx->opt.storage == LBM_MOM ? (unsigned char *)(a + P.off_xmark) : nullptr;
     p.wt = (double *)(a + P.off_wt);
     p.dsh = (float *)(a + P.off_dsh);
     p.rpop = (float *)(a + P.off_rpop);
@@ -659,6 +663,19 @@ int32_t lbm_init(const lbm_case *cases, const lbm_body *bodies, int32_t n_cases,
             for (int k = 0; k < 3; k++) B.org[k] = (int)std::floor(B.r[k] - B.Rb) - 2;
         }
     }
+    // the fixed part of the tile table: marker stencils, then surface points
+    std::vector<TileBox> tb(2 * P.mtiles.size(), TileBox{});
+    for (size_t t = 0; t < tb.size(); t++) {
+        const MarkerTile &mt = P.mtiles[t % P.mtiles.size()];
+        const CaseDev &d = P.cd[mt.c];
+        tb[t].c = mt.c;
+        tb[t].first = mt.first;
+        tb[t].count = mt.count;
+        tb[t].L = d.L;
+        tb[t].tile_off = d.tile_off;
+        tb[t].surface = d.force_offset > 0.0;
+        tb[t].reg_off = d.reg_off;
+    }
     hipStream_t s = ctx->stream;
     const size_t popb = (size_t)P.pop_elems * eb;
     hipError_t he;
@@ -674,8 +691,9 @@ int32_t lbm_init(const lbm_case *cases, const lbm_body *bodies, int32_t n_cases,
         (he = hipMemcpyAsync(p.dS, dS.data(), sizeof(double) * dS.size(), hipMemcpyHostToDevice, s)) != hipSuccess ||
         (he = hipMemcpyAsync(p.dSo, dSo.data(), sizeof(double) * dSo.size(), hipMemcpyHostToDevice, s)) != hipSuccess ||
         (P.mtiles.size() &&
-         (he = hipMemcpyAsync(p.mtiles, P.mtiles.data(), sizeof(MarkerTile) * P.mtiles.size(), hipMemcpyHostToDevice,
-                              s)) != hipSuccess) ||
+         ((he = hipMemcpyAsync(p.mtiles, P.mtiles.data(), sizeof(MarkerTile) * P.mtiles.size(), hipMemcpyHostToDevice,
+                               s)) != hipSuccess ||
+          (he = hipMemcpyAsync(p.tbox, tb.data(), sizeof(TileBox) * tb.size(), hipMemcpyHostToDevice, s)) != hipSuccess)) ||
         (he = hipStreamSynchronize(s)) != hipSuccess)
         return bail(LBM_EHIP, std::string("init: ") + hipGetErrorString(he));
     // side stream of the coupling (default priority, no implicit

@@ -76,12 +76,20 @@ struct Tile {
 struct MarkerTile {
     int c, first, count, pad;
 };
-// Box of region cells covering the stencils of a tile's markers.
+// A tile's entry of the tile table: the box of region cells covering the
+// stencils of its markers (or of its force-surface points), written by
+// k_markers every step, beside what else the tile kernels need of the tile and
+// its case, fixed at set-up, so that one load gives them every address.
 struct TileBox {
     int lo[3];    // first stencil node of the box (physical cell coordinates, x/y unwrapped)
-    int o[3];     // the same as region coordinates
     int e[3];     // box extent
+    int inv[2];   // 2^16 / e, rounded up: quotients by e[0] and e[1] as products
+    int base;     // region cell of the box's first cell
     int fits;     // 1 if the box has at most kBoxCells cells and lies inside the region
+    int c, first, count;      // case and markers of the tile
+    int L, tile_off;          // region edge and first tile of the case
+    int surface;              // 1: the case's force is taken on its force surface
+    long long reg_off;        // cell offset of the case region in the region pool
 };
 constexpr int kTileMarkers = 16;
 constexpr double kTileSpan = 3.0;
@@ -117,7 +125,9 @@ struct DevPtrs {
     double *part;    // per-tile force, torque and pressure-force sums (kPart each)
     double *res;     // per-tile max residual of the last interpolation
     double *wt;      // per-marker one-dimensional stencil weights, w[4 d + o] for node floor(X_d) - 1 + o
-    unsigned char *mark;   // per region cell: 1 if inside a tile's stencil box this step
+    unsigned char *mark;    // per region cell: 1 if inside the box of a tile's marker stencils this step
+    unsigned char *mark2;   // the same for the force-surface points
+    unsigned char *xmark;   // moment storage: per cell of the region and its rim, 1 if the gather pulls from it (else null)
     float *reg;
     long long *H;    // kHBufs fixed-point immersed-force accumulators, hstride elements apart
     long long hstride;
@@ -128,7 +138,7 @@ struct DevPtrs {
     double *hk2;     // per-marker final h of the step before the previous one (3)
     double *hs;      // per-marker scale of the warm-start features, |h0| + |h(t-1)|
     double *dSo;     // per-marker areas of the parallel force surface (cases with force_offset > 0)
-    TileBox *tbox;   // per-tile boxes of the markers' stencils, then of the force-surface points', by k_markers
+    TileBox *tbox;   // per tile, the markers' stencils, then per tile the force-surface points'
     float *dsh;      // moment storage: per region cell the forcing shift (Delta_x, Delta_y, Delta_z, lambda)
     float *rpop;     // moment storage: collided populations of the region and a one-cell rim, [27][xstride]
     long long xstride;

@@ -29,6 +29,9 @@
 #include "moments.hpp"
 #include <type_traits>
 
+// Register budget of the coupling's kernels (the reason stands at the tile kernels).
+#define EIGHT_WAVES __attribute__((amdgpu_waves_per_eu(8, 8)))
+
 namespace turret {
 
 
@@ -168,19 +171,52 @@ struct CodecMom {
     using T = float;
 };
 
-// Moment storage, first pass of the region gather: the collided populations
-// (forcing shifts included) of every cell of the particle region and a
-// one-cell rim, edge E = L + 2, into rpop.  Rim planes beyond a z wall are
-// never pulled and are left alone.
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) k_region_expand_mom(const float *__restrict__ src, DevPtrs p)
+// Work list of a region pass.  Only some of a region's cells take part in a
+// step (a sixth at the 256 x 256 x 768 ellipsoid), so a workgroup looks through
+// its cells, one per thread, and the ones that are wanted go to its first
+// threads: most wavefronts end at once, which counts where the rest wait for
+// slots that the lattice kernel frees.  More cells per workgroup pack them
+// closer but leave a small region too few workgroups (1024 cells: 119 us a step
+// instead of 101 in a 53 x 117 x 123 box, and nothing gained at the ellipsoid).
+// Returns the cell of thread k < n of the workgroup's 256 cells first .., -1 for
+// the others.  (At the ellipsoid 9 us a step on moment storage, 3 us on FP32,
+// against a thread per cell; nothing either way in small boxes.)
+struct ScanList {
+    unsigned char at[256];
+    int n[4];
+};
+
+__device__ inline int scan_cells(ScanList &l, int first, bool want)
 {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const unsigned long long m = __ballot(want);
+    if (lane == 0) l.n[w] = __popcll(m);
+    __syncthreads();
+    int at = 0;
+    for (int j = 0; j < w; j++) at += l.n[j];
+    if (want) l.at[at + __popcll(m & ((1ull << lane) - 1))] = (unsigned char)threadIdx.x;
+    __syncthreads();
+    const int n = l.n[0] + l.n[1] + l.n[2] + l.n[3];
+    return (int)threadIdx.x < n ? first + l.at[threadIdx.x] : -1;
+}
+
+// Moment storage, first pass of the region gather: the collided populations
+// (forcing shifts included) of the cells that the gather pulls from (marked by
+// k_markers in the region with a one-cell rim, edge E = L + 2), into rpop.  Rim
+// planes beyond a z wall are never pulled and are left alone.
+__global__ void __launch_bounds__(256) EIGHT_WAVES k_region_expand_mom(const float *__restrict__ src, DevPtrs p)
+{
+    __shared__ ScanList list;
     const int c = blockIdx.y;
     const CaseDev cd = p.cases[c];
     const BodyView B = body_view(p.body[c]);
-    if (cd.M == 0 || B.err != 0) return;
-    const int E = cd.L + 2, E3 = E * E * E;
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= E3) return;
+    const int E = cd.L + 2, E3 = E * E * E, first = blockIdx.x * 256;
+    if (cd.M == 0 || B.err != 0 || first >= E3) return;
+    unsigned char *mk = p.xmark + cd.xreg_off;
+    const int i0 = first + threadIdx.x;
+    const int q = scan_cells(list, first, i0 < E3 && mk[i0]);
+    if (q < 0) return;
+    mk[q] = 0;
     const int a = q % E, b = (q / E) % E, cc = q / (E * E);
     int z = B.org[2] - 1 + cc;
     if (z < 0 || z >= cd.nz) {
@@ -193,7 +229,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))
     const float *sp = src + cd.pop_off + ((long long)slot * cd.ny + y) * cd.nx + x;
     float m[10], sh[4], out[Q];
 #pragma unroll
-    for (int k = 0; k < 10; k++) m[k] = sp[k * cd.plane];
+    for (int i = 0; i < 10; i++) m[i] = sp[i * cd.plane];
     (void)mom::shift_at(mom::shift_box(p, cd, p.body[c]), cd.nx, cd.ny, cd.nz, x, y, slot, sh);
     mom::expand(m, sh, out);
     float *dst = p.rpop + cd.xreg_off + q;
@@ -207,51 +243,47 @@ __device__ inline void pull_region(const DevPtrs &p, const CaseDev &cd, int a, i
 {
     const int E = cd.L + 2;
     const float *R = p.rpop + cd.xreg_off;
-    const int wlo = z == 0 && cd.bc_lo != BC_PERIODIC, whi = z == cd.nz - 1 && cd.bc_hi != BC_PERIODIC;
+    const int cell = ((cc + 1) * E + b + 1) * E + a + 1;
     Unroll<0, Q>::run([&](auto I) {
         constexpr int i = decltype(I)::value;
-        int sa = a + 1 - cx(i), sb = b + 1 - cy(i), sc = cc + 1 - cz(i);
-        int dir = i;
-        float sign = 1.0f, add = 0.0f;
+        g[i] = R[i * p.xstride + (cell - (cz(i) * E + cy(i)) * E - cx(i))];
+    });
+    // cells at a wall: the populations that come from beyond it again
+    const bool wlo = z == 0 && cd.bc_lo != BC_PERIODIC, whi = z == cd.nz - 1 && cd.bc_hi != BC_PERIODIC;
+    if (!wlo && !whi) return;
+    Unroll<0, Q>::run([&](auto I) {
+        constexpr int i = decltype(I)::value;
         if constexpr (cz(i) != 0) {
-            const bool wall = cz(i) == 1 ? wlo : whi;
+            if (!(cz(i) == 1 ? wlo : whi)) return;
             const int bc = cz(i) == 1 ? cd.bc_lo : cd.bc_hi;
-            if (wall) {
-                sc = cc + 1;
-                if (bc == BC_FREESLIP) {
-                    dir = mirror_z(i);
-                } else {
-                    dir = opposite(i);
-                    sa = a + 1;
-                    sb = b + 1;
-                    if (bc == BC_PRESSURE) sign = -1.0f;
-                    else if constexpr (cx(i) != 0) add = (float)(6.0 * wq(i) * cx(i)) * (cz(i) == 1 ? cd.uw_lo : cd.uw_hi);
-                }
+            if (bc == BC_FREESLIP) {
+                g[i] = R[mirror_z(i) * p.xstride + (cell - cy(i) * E - cx(i))];
+                return;
             }
+            const float v = R[opposite(i) * p.xstride + cell];
+            if (bc == BC_PRESSURE) g[i] = -v;
+            else if constexpr (cx(i) != 0) g[i] = v + (float)(6.0 * wq(i) * cx(i)) * (cz(i) == 1 ? cd.uw_lo : cd.uw_hi);
+            else g[i] = v;
         }
-        g[i] = sign * R[dir * p.xstride + ((long long)sc * E + sb) * E + sa] + add;
     });
 }
 
 // ------------------------------------------------------------ region fields
-// For every cell of the particle region: pull f(t+1) from the buffer the
-// lattice kernel read, then rho - 1, u* = sum xi f / sum f and the stress
-// sigma = -p I + (1/(2 tau) - 1) P1 with p = cs^2 (rho - 1) (Sec. 2.1).
-// Also clears the fixed-point immersed-force accumulators.  Only cells marked
-// by k_markers (inside some tile's stencil box) are visited; the others are
-// read by no interpolation and carry no force.
-template <class CD>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) k_region_gather(const typename CD::T *__restrict__ src, DevPtrs p, int sid)
+// For every marked cell of the particle region (inside some tile's stencil box;
+// the others are read by no interpolation and carry no force): pull f(t+1) from
+// the buffer the lattice kernel read, then rho - 1, u* = sum xi f / sum f and
+// the stress sigma = -p I + (1/(2 tau) - 1) P1 with p = cs^2 (rho - 1)
+// (Sec. 2.1).  Also clears the cells' fixed-point immersed-force accumulators
+// and the marks of the force-surface points (the correction clears the others).
+// One region cell; fetch(cd, x, y, z, g) gives the populations pulled by the
+// cell at (x, y, z).
+template <class Fetch>
+__device__ __forceinline__ void gather_cell(const DevPtrs &p, const CaseDev &cd, const int org[3], int q, Fetch &&fetch)
 {
-    const int c = blockIdx.y;
-    const CaseDev cd = p.cases[c];
-    const BodyView B = body_view(p.body[c]);
-    if (cd.M == 0 || B.err != 0) return;
     const int L = cd.L, L3 = L * L * L;
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= L3 || !p.mark[cd.reg_off + q]) return;
     float *R = p.reg + cd.reg_off * kRegFields;
     long long *H = p.H + cd.reg_off * 3;
+    p.mark2[cd.reg_off + q] = 0;
 #pragma unroll
     for (int j = 0; j < kHBufs; j++) {
         H[j * p.hstride + q] = 0;
@@ -259,26 +291,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))
         H[j * p.hstride + 2 * L3 + q] = 0;
     }
     const int a = q % L, b = (q / L) % L, cc = q / (L * L);
-    const int gz = B.org[2] + cc;
+    const int gz = org[2] + cc;
     if (gz < 0 || gz >= cd.nz) {
 #pragma unroll
         for (int f = 0; f < kRegFields; f++) R[f * L3 + q] = 0.0f;
         return;
     }
-    const int gx = wrapi(B.org[0] + a, cd.nx), gy = wrapi(B.org[1] + b, cd.ny);
     float g[Q];
-    if constexpr (std::is_same<CD, CodecMom>::value) {
-        pull_region(p, cd, a, b, cc, gz, g);
-    } else if (cd.LB[0] > 0) {
-        // reduced-precision store with a full-precision box around the body
-        const BodyDev &Bd = p.body[c];
-        const int fo[3] = {Bd.fo[sid][0], Bd.fo[sid][1], Bd.fo[sid][2]};
-        pull_fine<CD>(src + cd.pop_off, Bd.fvalid[sid] ? p.fine[sid] + cd.fine_off : nullptr, cd, B.z0, fo, gx, gy, gz,
-                      g);
-    } else {
-        pull<CD>(src + cd.pop_off, cd.plane, cd.nx, cd.ny, cd.nz, B.z0, cd.bc_lo, cd.bc_hi, cd.uw_lo, cd.uw_hi, gx, gy,
-                 gz, g);
-    }
+    fetch(a, b, cc, gz, g);
     const Macro M = macro(raw_moments(g));
     const float tau = tau_at(cd.tau0, cd.nz, cd.sponge, gz);
     const float fac = 0.5f / tau - 1.0f;
@@ -293,6 +313,41 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))
     R[7 * L3 + q] = fac * M.P[0][1];
     R[8 * L3 + q] = fac * M.P[0][2];
     R[9 * L3 + q] = fac * M.P[1][2];
+}
+
+// src: the buffer the lattice kernel read (moment storage: unused, the cells
+// pull from the expanded region).
+template <class CD>
+__global__ void __launch_bounds__(256) EIGHT_WAVES k_region_gather(const typename CD::T *__restrict__ src, DevPtrs p, int sid)
+{
+    __shared__ ScanList list;
+    const int c = blockIdx.y;
+    const CaseDev cd = p.cases[c];
+    const BodyView B = body_view(p.body[c]);
+    const int L3 = cd.L * cd.L * cd.L, first = blockIdx.x * 256;
+    if (cd.M == 0 || B.err != 0 || first >= L3) return;
+    const long long i0 = cd.reg_off + min(first + (int)threadIdx.x, L3 - 1);
+    const int q = scan_cells(list, first, (p.mark[i0] | p.mark2[i0]) != 0 && first + (int)threadIdx.x < L3);
+    if (q < 0) return;
+    gather_cell(p, cd, B.org, q, [&](int a, int b, int cc, int gz, float g[Q]) {
+        if constexpr (std::is_same<CD, CodecMom>::value) {
+            pull_region(p, cd, a, b, cc, gz, g);
+        } else {
+            const int gx = wrapi(B.org[0] + a, cd.nx), gy = wrapi(B.org[1] + b, cd.ny);
+            if constexpr (!std::is_same<CD, CodecF32>::value) {
+                if (cd.LB[0] > 0) {
+                    // reduced-precision store with a full-precision box around the body
+                    const BodyDev &Bd = p.body[c];
+                    const int fo[3] = {Bd.fo[sid][0], Bd.fo[sid][1], Bd.fo[sid][2]};
+                    pull_fine<CD>(src + cd.pop_off, Bd.fvalid[sid] ? p.fine[sid] + cd.fine_off : nullptr, cd, B.z0, fo, gx,
+                                  gy, gz, g);
+                    return;
+                }
+            }
+            pull<CD>(src + cd.pop_off, cd.plane, cd.nx, cd.ny, cd.nz, B.z0, cd.bc_lo, cd.bc_hi, cd.uw_lo, cd.uw_hi, gx, gy,
+                     gz, g);
+        }
+    });
 }
 
 // --------------------------------------------------------- marker stencils
@@ -314,7 +369,7 @@ struct Node {
     double W;     // tensor-product weight
 };
 
-__device__ inline Node stencil_node(const double X[3], int lane, const CaseDev &cd, const BodyView &B)
+__device__ inline Node stencil_node(const double X[3], int lane, const CaseDev &cd, const int org[3])
 {
     const int off[3] = {lane & 3, (lane >> 2) & 3, lane >> 4};
     const int n[3] = {cd.nx, cd.ny, cd.nz};
@@ -327,7 +382,7 @@ __device__ inline Node stencil_node(const double X[3], int lane, const CaseDev &
     for (int d = 0; d < 3; d++) {
         const int node = (int)floor(X[d]) - 1 + off[d];
         nd.W *= phi4((double)node - X[d]);
-        int rel = node - B.org[d];
+        int rel = node - org[d];
         if (d < 2) rel = wrapi(rel, n[d]);
         ok = ok && rel >= 0 && rel < L;
         r[d] = rel;
@@ -420,27 +475,28 @@ struct Column {
     double W[4];    // node weights
 };
 
-// The column's nodes from the marker's one-dimensional weights w (box path;
-// W = (w_x w_y) w_z, the product order of box_node_w) or from stencil_node.
-__device__ inline Column column_nodes(const double X[3], const double *w, int col, const TileBox &tb,
-                                      const CaseDev &cd, const BodyView &B)
+// The column's nodes: in a box that fits from the column's one-dimensional
+// weights w(x, y, z level) = wx, wy, wz[4] (W = (w_x w_y) w_z, the product order
+// of box_node_w), else from stencil_node.
+__device__ inline Column column_nodes(const DevPtrs &p, const double X[3], double wx, double wy, const double wz[4], int col,
+                                      const TileBox &tb)
 {
     Column cn;
     const int cx = col & 3, cy = col >> 2;
     if (tb.fits) {
-        const double wxy = (1.0 * w[cx]) * w[4 + cy];
+        const double wxy = wx * wy;
         const int b0 = ((int)floor(X[0]) - 1 + cx - tb.lo[0]) +
                        tb.e[0] * (((int)floor(X[1]) - 1 + cy - tb.lo[1]) + tb.e[1] * ((int)floor(X[2]) - 1 - tb.lo[2]));
 #pragma unroll
         for (int z = 0; z < 4; z++) {
-            cn.W[z] = wxy * w[8 + z];
+            cn.W[z] = wxy * wz[z];
             cn.i[z] = b0 + z * tb.e[0] * tb.e[1];
             cn.q[z] = -1;
         }
     } else {
 #pragma unroll
         for (int z = 0; z < 4; z++) {
-            const Node nd = stencil_node(X, col + 16 * z, cd, B);
+            const Node nd = stencil_node(X, col + 16 * z, p.cases[tb.c], p.body[tb.c].org);
             cn.W[z] = nd.W;
             cn.q[z] = nd.q;
             cn.i[z] = 0;
@@ -449,16 +505,17 @@ __device__ inline Column column_nodes(const double X[3], const double *w, int co
     return cn;
 }
 
-// Region cell index of box cell i.
-__device__ inline int box_region_cell(int i, const TileBox &b, int L)
+// Region cell index of cell i of a box that fits (quotients by the
+// multiplication that wave_box's caller prepared: exact for i < 2^16 / e).
+__device__ inline int box_region_cell(int i, const TileBox &b)
 {
-    const int bx = i % b.e[0], t = i / b.e[0], by = t % b.e[1], bz = t / b.e[1];
-    return (b.o[0] + bx) + L * ((b.o[1] + by) + L * (b.o[2] + bz));
+    const int t = (i * b.inv[0]) >> 16, bx = i - t * b.e[0], bz = (t * b.inv[1]) >> 16, by = t - bz * b.e[1];
+    return b.base + bx + b.L * (by + b.L * bz);
 }
 
 // Marks stencil node `lane` of the point X as used in this step (region
 // cells outside every stencil are neither gathered nor corrected).
-__device__ inline void mark_node(const DevPtrs &p, const CaseDev &cd, const BodyView &B, const double X[3], int lane)
+__device__ inline void mark_node(unsigned char *mk, unsigned char *xmk, const CaseDev &cd, const BodyView &B, const double X[3], int lane)
 {
     const int off[3] = {lane & 3, (lane >> 2) & 3, lane >> 4};
     const int n[3] = {cd.nx, cd.ny, cd.nz};
@@ -472,7 +529,11 @@ __device__ inline void mark_node(const DevPtrs &p, const CaseDev &cd, const Body
         ok = ok && rel >= 0 && rel < L;
         r[d] = rel;
     }
-    if (ok) p.mark[cd.reg_off + r[0] + L * (r[1] + L * r[2])] = 1;
+    if (!ok) return;
+    mk[r[0] + L * (r[1] + L * r[2])] = 1;
+    if (xmk)
+        for (int n = 0; n < 27; n++)
+            xmk[r[0] + n % 3 + (L + 2) * (r[1] + n / 3 % 3 + (L + 2) * (r[2] + n / 9))] = 1;
 }
 
 // Box of the stencil nodes of the points P held by the lanes with `on` set
@@ -494,40 +555,59 @@ __device__ inline void wave_box(const double P[3], bool on, int lo[3], int e[3])
     }
 }
 
-// Marks the stencil cells of the tile's points P (lane j < count holds
-// point j): the whole box when it lies inside the region, else node by node.
-// Returns the box as a TileBox.
-__device__ inline TileBox mark_points(const DevPtrs &p, const CaseDev &cd, const BodyView &B, const double P[3],
-                                      int count, int lane)
+// Marks in mk the stencil cells of the tile's points P (lane j < count holds
+// point j): the whole box when it lies inside the region, else node by node;
+// and in xmk (moment storage) those and their neighbours.
+// The box goes to the tile's entry of the tile table.
+__device__ inline void mark_points(unsigned char *mk, unsigned char *xmk, const CaseDev &cd, const BodyView &B,
+                                   const double P[3], int count, int lane, TileBox &out)
 {
-    TileBox b;
-    wave_box(P, lane < count, b.lo, b.e);
+    int lo[3], e[3], o[3];
+    wave_box(P, lane < count, lo, e);
     const int L = cd.L;
     bool in = true;
 #pragma unroll
     for (int d = 0; d < 3; d++) {
-        b.o[d] = b.lo[d] - B.org[d];
-        in = in && b.o[d] >= 0 && b.o[d] + b.e[d] <= L;
+        o[d] = lo[d] - B.org[d];
+        in = in && o[d] >= 0 && o[d] + e[d] <= L;
     }
-    const int n = b.e[0] * b.e[1] * b.e[2];
-    b.fits = in && n <= kBoxCells;
+    const int base = o[0] + L * (o[1] + L * o[2]);
     if (in) {
-        unsigned char *mk = p.mark + cd.reg_off;
-        for (int i = lane; i < n; i += 64) mk[box_region_cell(i, b, L)] = 1;
+        for (int r = lane; r < e[0] * e[1]; r += 64) {
+            const int by = r / e[0], at = base + (r - by * e[0]) + L * by;
+            for (int bz = 0; bz < e[2]; bz++) mk[at + L * L * bz] = 1;
+        }
+        if (xmk) {   // the same box with a one-cell rim, in the region with its rim
+            const int E = L + 2, e0 = e[0] + 2, n = e0 * (e[1] + 2);
+            for (int r = lane; r < n; r += 64) {
+                const int by = r / e0, at = o[0] + (r - by * e0) + E * (o[1] + by + E * o[2]);
+                for (int bz = 0; bz < e[2] + 2; bz++) xmk[at + E * E * bz] = 1;
+            }
+        }
     } else {
         for (int j = 0; j < count; j++) {
             const double Pj[3] = {__shfl(P[0], j), __shfl(P[1], j), __shfl(P[2], j)};
-            mark_node(p, cd, B, Pj, lane);
+            mark_node(mk, xmk, cd, B, Pj, lane);
         }
     }
-    return b;
+    if (lane == 0) {
+#pragma unroll
+        for (int d = 0; d < 3; d++) {
+            out.lo[d] = lo[d];
+            out.e[d] = e[d];
+        }
+        out.inv[0] = (65535 + e[0]) / e[0];
+        out.inv[1] = (65535 + e[1]) / e[1];
+        out.base = base;
+        out.fits = in && e[0] * e[1] * e[2] <= kBoxCells;
+    }
 }
 
 // One wavefront per marker tile (Sec. 2.3 kinematics): lane j < count forms
 // the position, normal and rigid velocity of marker first + j and checks the
 // z range; the tile's stencil box goes to the tile table, and the cells of
 // that box (and of the force-surface points' box) are marked for this step.
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) k_markers(DevPtrs p, int n_mtiles)
+__global__ void __launch_bounds__(64) EIGHT_WAVES k_markers(DevPtrs p, int n_mtiles)
 {
     const int tix = tile_of_block((int)blockIdx.x, n_mtiles);
     if (tix >= n_mtiles) return;
@@ -572,70 +652,102 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8)))
             if (gz - 1 < 0 || gz + 2 > cd.nz - 1) atomicOr(&p.body[mt.c].err, 1);
         }
     }
-    const TileBox tb = mark_points(p, cd, B, X, mt.count, lane);
-    if (lane == 0) p.tbox[tix] = tb;
-    if (dl > 0.0) {
+    unsigned char *xmk = p.xmark ? p.xmark + cd.xreg_off : nullptr;
+    mark_points(p.mark + cd.reg_off, xmk, cd, B, X, mt.count, lane, p.tbox[tix]);
+    if (dl > 0.0) {   // the force-surface points
         const double Y[3] = {X[0] + dl * N[0], X[1] + dl * N[1], X[2] + dl * N[2]};
-        const TileBox to = mark_points(p, cd, B, Y, mt.count, lane);
-        if (lane == 0) p.tbox[n_mtiles + tix] = to;   // the force-surface points' box
+        mark_points(p.mark2 + cd.reg_off, xmk, cd, B, Y, mt.count, lane, p.tbox[n_mtiles + tix]);
     }
 }
 
-// Per-marker epilogue of the l = 0 interpolation: plain start, features and
-// the stress-integral parts into o[kPart] (vin = interpolated rho - 1, u*,
-// sigma; o may alias vin).  h_k becomes h0 when the first spread has been
-// done (spread set), else 0.
-__device__ inline void force_epilogue(const DevPtrs &p, int k, const BodyView &B, const double *vin, double *o,
-                                      int spread)
-{
-    double v[kRegFields];
-#pragma unroll
-    for (int f = 0; f < kRegFields; f++) v[f] = vin[f];
-    const double X[3] = {p.X[3 * k], p.X[3 * k + 1], p.X[3 * k + 2]};
-    const double pr = (double)CS2 * v[0];
-    const double sg[3][3] = {{v[4], v[7], v[8]}, {v[7], v[5], v[9]}, {v[8], v[9], v[6]}};
-    const double nk[3] = {p.N[3 * k], p.N[3 * k + 1], p.N[3 * k + 2]};
-    const double dS = p.dS[k];
-    double s[3], rel[3], ts[3], h0[3], hp[3], hq[3], h0q[3];
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-        h0[a] = p.U[3 * k + a] - v[1 + a];
-        hp[a] = p.hk[3 * k + a];    // the previous step's final h
-        hq[a] = p.hk2[3 * k + a];   // the final h of the step before
-        h0q[a] = p.h0[3 * k + a];   // the previous step's plain start
+// Epilogue of the l = 0 interpolation: plain start, warm-start features and the
+// stress-integral parts, by one wavefront, four lanes per marker: lane a < 3 of
+// a marker's quad takes component a (lane 3 repeats component 0 and stores
+// nothing).  Its operands load with the tile's other data; one thread per
+// marker, which held all components at once, spilled 24 registers.
+struct Epilogue {
+    int j, a, k;          // marker of the tile, component, marker
+    bool on;
+    double hp, hq, h0q;   // the final h of the previous step and of the one before, the previous plain start
+    double n;             // the normal
+    __device__ inline void load(const DevPtrs &p, const TileBox &tb)
+    {
+        j = (threadIdx.x & 63) >> 2;
+        a = threadIdx.x & 3;
+        on = threadIdx.x < 64 && j < tb.count && a < 3;
+        a = a < 3 ? a : 0;
+        k = tb.first + (j < tb.count ? j : 0);
+        hp = hq = h0q = n = 0.0;
+        if (threadIdx.x < 64) {
+            hp = p.hk[3 * k + a];
+            hq = p.hk2[3 * k + a];
+            h0q = p.h0[3 * k + a];
+            n = p.N[3 * k + a];
+        }
     }
+};
+
+// Value of lane a of this lane's quad.
+template <int A>
+__device__ inline double quad_lane(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, A * 0x55, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), A * 0x55, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ inline double quad_at(double v, int a)
+{
+    const double v0 = quad_lane<0>(v), v1 = quad_lane<1>(v), v2 = quad_lane<2>(v);
+    return a == 0 ? v0 : (a == 1 ? v1 : v2);
+}
+__device__ inline double quad_norm(double v)
+{
+    const double v0 = quad_lane<0>(v), v1 = quad_lane<1>(v), v2 = quad_lane<2>(v);
+    return sqrt(v0 * v0 + v1 * v1 + v2 * v2);
+}
+
+// One wavefront: ev = a marker's interpolated rho - 1, u*, sigma (rewritten as
+// its parts), rec = its record, r = the body's centre.  h_k becomes h0 when the
+// first spread has been done (spread set), else 0.
+template <int W>
+__device__ inline void force_epilogue(const DevPtrs &p, const Epilogue &E, const double r[3], double (*ev)[kRegFields],
+                                      const double (*rec)[W], int spread)
+{
+    const int a = E.a, b = a == 2 ? 0 : a + 1, c = b == 2 ? 0 : b + 1, j = E.on ? E.j : 0, k = E.k;
+    const double *v = ev[j], *rc = rec[j];
+    const double h0 = rc[3 + a] - v[1 + a], dS = rc[6], pr = (double)CS2 * v[0];
+    // sigma's row a; fields 4..9 = xx yy zz xy xz yz
+    const double sx = v[a == 0 ? 4 : (a == 1 ? 7 : 8)], sy = v[a == 0 ? 7 : (a == 1 ? 5 : 9)], sz = v[a == 0 ? 8 : (a == 1 ? 9 : 6)];
+    const double s = sx * quad_lane<0>(E.n) + sy * quad_lane<1>(E.n) + sz * quad_lane<2>(E.n);
+    const double rel_b = rc[b] - r[b], rel_c = rc[c] - r[c];
+    const double ts = rel_b * quad_at(s, c) - rel_c * quad_at(s, b);
     // warm-start features: the plain start U - I[u*] (an invertible linear
     // map of I[u*] and U that keeps their small difference out of
     // cancellation), h(t-1), and the changes h(t-1) - h(t-2) and
     // h0(t) - h0(t-1), over the marker's scale |h0| + |h(t-1)|; the normal
     // and the area
-    const double sc = fmax(sqrt(h0[0] * h0[0] + h0[1] * h0[1] + h0[2] * h0[2]) +
-                               sqrt(hp[0] * hp[0] + hp[1] * hp[1] + hp[2] * hp[2]), 1e-14);
-    p.hs[k] = sc;
+    const double sc = fmax(quad_norm(h0) + quad_norm(E.hp), 1e-14);
+    if (!E.on) return;
     float *ft = p.feat + (long long)kMlpIn * k;
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-        s[a] = sg[a][0] * nk[0] + sg[a][1] * nk[1] + sg[a][2] * nk[2];
-        rel[a] = X[a] - B.r[a];
-        ft[kFeatH0 + a] = (float)(h0[a] / sc);
-        ft[kFeatHPrev + a] = (float)(hp[a] / sc);
-        ft[kFeatDH + a] = (float)((hp[a] - hq[a]) / sc);
-        ft[kFeatDH0 + a] = (float)((h0[a] - h0q[a]) / sc);
-        ft[kFeatNormal + a] = (float)nk[a];
-        if (a == 0) ft[kFeatArea] = (float)dS;
-        // h_k holds what has been spread so far; dh is the next increment
-        p.hk2[3 * k + a] = hp[a];
-        p.h0[3 * k + a] = h0[a];
-        p.hk[3 * k + a] = spread ? 0.0 + h0[a] : 0.0;
-        p.dh[3 * k + a] = h0[a];
+    ft[kFeatH0 + a] = (float)(h0 / sc);
+    ft[kFeatHPrev + a] = (float)(E.hp / sc);
+    ft[kFeatDH + a] = (float)((E.hp - E.hq) / sc);
+    ft[kFeatDH0 + a] = (float)((h0 - E.h0q) / sc);
+    ft[kFeatNormal + a] = (float)E.n;
+    if (a == 0) {
+        ft[kFeatArea] = (float)dS;
+        p.hs[k] = sc;
     }
-    cross3(rel, s, ts);
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-        o[a] = dS * s[a];
-        o[3 + a] = dS * ts[a];
-        o[6 + a] = dS * (-pr) * nk[a];
-    }
+    // h_k holds what has been spread so far; dh is the next increment
+    p.hk2[3 * k + a] = E.hp;
+    p.h0[3 * k + a] = h0;
+    p.hk[3 * k + a] = spread ? 0.0 + h0 : 0.0;
+    p.dh[3 * k + a] = h0;
+    double *o = ev[E.j];   // (every lane of the wavefront has read its fields)
+    o[a] = dS * s;
+    o[3 + a] = dS * ts;
+    o[6 + a] = dS * (-pr) * E.n;
 }
 
 // Tile sums of the per-marker parts (the first kPart entries of each row of
@@ -644,7 +756,7 @@ template <int W>
 __device__ inline void tile_part_sum(const DevPtrs &p, int tix, int count, const double (*tp)[W])
 {
     __syncthreads();
-    if ((int)threadIdx.x < kPart) {
+    if (count > 0 && (int)threadIdx.x < kPart) {
         double acc = 0.0;
         for (int j = 0; j < count; j++) acc += tp[j][threadIdx.x];
         p.part[(long long)kPart * tix + threadIdx.x] = acc;
@@ -724,11 +836,11 @@ __device__ inline void spread_node(const DevPtrs &p, int c, const TileBox &tb, i
 
 // The tile's LDS accumulator into the region accumulator: one global atomic
 // per touched cell and component (after a barrier).
-__device__ inline void spread_flush(const TileBox &tb, int ncell, int L, int L3,
-                                    const unsigned long long (*acc)[kBoxCells], long long *Hc)
+__device__ inline void spread_flush(const TileBox &tb, int ncell, int L3, const unsigned long long (*acc)[kBoxCells],
+                                    long long *Hc)
 {
     for (int i = threadIdx.x; i < ncell; i += blockDim.x) {
-        const int q = box_region_cell(i, tb, L);
+        const int q = box_region_cell(i, tb);
 #pragma unroll
         for (int a = 0; a < 3; a++)
             if (acc[a][i] != 0ull) atomicAdd((unsigned long long *)&Hc[a * L3 + q], acc[a][i]);
@@ -739,18 +851,13 @@ __device__ inline void spread_flush(const TileBox &tb, int ncell, int L, int L3,
 // weights (7..18), h_k (19..21).  The force kernel keeps entries 0..18.
 constexpr int kRecW = 7, kRecH = 19, kRecForce = 19, kRecUpdate = 22;
 
-// The tile kernels of the coupling run beside the lattice kernel, whose waves
-// each hold 64 VGPRs and 96 SGPRs and fill every wave slot of a SIMD.  A
-// coupling wave starts only in a slot a lattice wave frees, so the force and
-// update passes come in two register budgets, MINW = 8 waves per SIMD (the
-// lattice kernel's own budget) and MINW = 1 (registers as the LDS-bound
-// occupancy allows).
-// FP32 storage takes the first: measured at the 256 x 256 x 768 case, its
-// coupling then runs during the lattice kernel instead of after it, 50 us
-// less per step.  With FP16 storage the coupling already runs beside the
-// lattice kernel and the tighter budget only slows that kernel, so the
-// reduced-precision and moment stores take the second.  The LDS of these
-// kernels is taken at launch (dynamic), so that the compiler's occupancy
+// The kernels of the coupling run beside the lattice kernel, whose waves each
+// hold 64 VGPRs and 96 SGPRs and fill every wave slot of a SIMD (the moment
+// step: 14 waves of 128 VGPRs).  A coupling wave starts only in a slot that is
+// free, so they are compiled for 8 waves per SIMD, the lattice kernel's own
+// budget: at 256 x 256 x 768 the coupling then runs during the lattice kernel
+// instead of after it, 50 us less per step in FP32, 60 in BF16.  The LDS of the
+// tile kernels is taken at launch (dynamic), so that the compiler's occupancy
 // target is set by the register budget and not by the LDS size; the layouts
 // are carved below, 8-byte arrays first.
 
@@ -768,14 +875,11 @@ struct LdsCarve {
 constexpr size_t kLdsForce = sizeof(unsigned long long[3][kBoxCells]) + sizeof(double[kTileMarkers][kRegFields]) +
                              sizeof(double[kTileMarkers][kRecForce]) + sizeof(double[kTileMarkers][3]) +
                              sizeof(float[kRegFields][kBoxCells]);
+constexpr size_t kLdsSurface = sizeof(double[kTileMarkers][7]) + sizeof(double[kTileMarkers][kPart]) + sizeof(float[7][kBoxCells]);
 constexpr size_t kLdsUpdate = sizeof(double[3][kBoxCells]) + sizeof(unsigned long long[3][kBoxCells]) +
                               sizeof(double[kTileMarkers][kRecUpdate]) + sizeof(double[kTileMarkers][3]) +
                               sizeof(double[kTileMarkers]);
-static_assert(kLdsForce <= 65536 && kLdsUpdate <= 65536, "tile kernel LDS");
-// Waves per SIMD that the LDS of a 256-thread workgroup allows (160 KB per
-// CU): the occupancy the unconstrained budget is compiled for, as with static
-// LDS.
-constexpr int lds_waves(size_t bytes) { return (int)std::min<size_t>(8, (160 * 1024) / bytes); }
+static_assert(kLdsForce <= 65536 && kLdsUpdate <= 65536 && kLdsSurface <= kLdsUpdate, "tile kernel LDS");
 __device__ inline double marker_record(const DevPtrs &p, int k, int f)
 {
     if (f < 3) return p.X[3 * k + f];
@@ -792,7 +896,7 @@ template <int NREC>
 struct RecordLoad {
     static_assert(kTileMarkers * NREC <= 512, "two loads per thread of a 256-thread workgroup");
     double v[2];
-    __device__ inline void load(const DevPtrs &p, const MarkerTile &mt)
+    __device__ inline void load(const DevPtrs &p, const TileBox &mt)
     {
 #pragma unroll
         for (int u = 0; u < 2; u++) {
@@ -800,7 +904,7 @@ struct RecordLoad {
             v[u] = t < mt.count * NREC ? marker_record(p, mt.first + t / NREC, t % NREC) : 0.0;
         }
     }
-    __device__ inline void store(const MarkerTile &mt, double (*rec)[NREC]) const
+    __device__ inline void store(const TileBox &mt, double (*rec)[NREC]) const
     {
 #pragma unroll
         for (int u = 0; u < 2; u++) {
@@ -813,12 +917,11 @@ struct RecordLoad {
 // Spread of the tile's per-marker increments d[j] (LDS rows) after a
 // barrier: wavefront w takes markers w, w+4, ...; lane l is stencil node l,
 // so the 64 LDS atomics of one instruction go to 64 different cells.
-__device__ inline void spread_tile(const DevPtrs &p, const MarkerTile &mt, const TileBox &tb, const CaseDev &cd,
-                                   const BodyView &B, const double *rbase, int nrec, const double (*d)[3],
-                                   unsigned long long (*acc)[kBoxCells], long long *Hc, int L3)
+__device__ inline void spread_tile(const DevPtrs &p, const TileBox &tb, const double *rbase, int nrec,
+                                   const double (*d)[3], unsigned long long (*acc)[kBoxCells], long long *Hc, int L3)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int j = wave; j < mt.count; j += blockDim.x >> 6) {
+    for (int j = wave; j < tb.count; j += blockDim.x >> 6) {
         const double *rc = rbase + j * nrec;
         const double X[3] = {rc[0], rc[1], rc[2]};
         double W;
@@ -826,58 +929,56 @@ __device__ inline void spread_tile(const DevPtrs &p, const MarkerTile &mt, const
         if (tb.fits) {
             i = box_node_w(X, rc + kRecW, lane, tb, W);
         } else {
-            const Node nd = stencil_node(X, lane, cd, B);
+            const Node nd = stencil_node(X, lane, p.cases[tb.c], p.body[tb.c].org);
             W = nd.W;
             q = nd.q;
         }
-        spread_node(p, mt.c, tb, i, q, W * rc[6], d[j], acc, Hc, L3);
+        spread_node(p, tb.c, tb, i, q, W * rc[6], d[j], acc, Hc, L3);
     }
 }
 
 // l = 0 and the stress integral over a tile (a row of 16 lanes per marker).
 // With spread set, also the first forcing cycle's spread of the plain start
-// h0 into accumulator 0 (h_k = h0).
-template <int MINW>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MINW, MINW == 8 ? 8 : lds_waves(kLdsForce))))
-k_interp_force_tiles(DevPtrs p, int n_mtiles, int spread)
+// h0 into accumulator 0 (h_k = h0).  The tile's force, torque and pressure
+// force go to its parts unless the case has a force surface.
+__device__ inline void force_tile(const DevPtrs &p, const TileBox &tb, int tix, int spread, unsigned char *lds)
 {
-    extern __shared__ __align__(16) unsigned char lds_dyn[];
-    LdsCarve lc{lds_dyn};
+    LdsCarve lc{lds};
     auto &acc = lc.take<unsigned long long[3][kBoxCells]>();
     auto &ep = lc.take<double[kTileMarkers][kRegFields]>();    // interpolated fields, then the marker's parts
     auto &mrec = lc.take<double[kTileMarkers][kRecForce]>();   // the tile's marker records
     auto &dinc = lc.take<double[kTileMarkers][3]>();           // the markers' increments (h0) to spread
     auto &box = lc.take<float[kRegFields][kBoxCells]>();
-    const int tix = tile_of_block((int)blockIdx.x, n_mtiles);
-    if (tix >= n_mtiles) return;
-    const MarkerTile mt = p.mtiles[tix];
-    const CaseDev cd = p.cases[mt.c];
-    const BodyView B = body_view(p.body[mt.c]);
-    if (B.err != 0) return;
-    const int L = cd.L, L3 = L * L * L;
-    const float *R = p.reg + cd.reg_off * kRegFields;
-    long long *H0 = p.H + cd.reg_off * 3;
-    const TileBox tb = p.tbox[tix];
+    const int L3 = tb.L * tb.L * tb.L;
+    const float *R = p.reg + tb.reg_off * kRegFields;
+    long long *H0 = p.H + tb.reg_off * 3;
     const int ncell = tb.e[0] * tb.e[1] * tb.e[2];
-    // the markers' records load in the same round as the box
+    // the markers' records, the epilogue's operands and the body load in the
+    // same round as the box
     RecordLoad<kRecForce> rl;
-    rl.load(p, mt);
+    rl.load(p, tb);
+    Epilogue ep_in;
+    ep_in.load(p, tb);
+    const BodyDev &B = p.body[tb.c];
+    const int err = B.err;
     if (tb.fits) {
         for (int i = threadIdx.x; i < ncell; i += blockDim.x) {
-            const int q = box_region_cell(i, tb, L);
+            const int q = box_region_cell(i, tb);
 #pragma unroll
             for (int f = 0; f < kRegFields; f++) box[f][i] = R[f * L3 + q];
             acc[0][i] = acc[1][i] = acc[2][i] = 0ull;
         }
     }
-    rl.store(mt, mrec);
+    if (err != 0) return;
+    rl.store(tb, mrec);
     __syncthreads();
     // rows past the tile's markers repeat marker 0 and store nothing
     const int j = threadIdx.x >> 4, col = threadIdx.x & 15;
-    const bool on = j < mt.count;
+    const bool on = j < tb.count;
     const double *rc = mrec[on ? j : 0];
     const double X[3] = {rc[0], rc[1], rc[2]};
-    const Column cn = column_nodes(X, rc + kRecW, col, tb, cd, B);
+    const double *wr = rc + kRecW;   // 4 weights per axis
+    const Column cn = column_nodes(p, X, wr[col & 3], wr[4 + (col >> 2)], wr + 8, col, tb);
     double v[kRegFields];
 #pragma unroll
     for (int f = 0; f < kRegFields; f++) v[f] = 0.0;
@@ -900,59 +1001,55 @@ k_interp_force_tiles(DevPtrs p, int n_mtiles, int spread)
         for (int a = 0; a < 3; a++) dinc[j][a] = rc[3 + a] - v[1 + a];
     }
     __syncthreads();
-    if (spread) spread_tile(p, mt, tb, cd, B, &mrec[0][0], kRecForce, dinc, acc, H0, L3);
-    // the tile's epilogues side by side, one thread per marker
-    if ((int)threadIdx.x < mt.count) force_epilogue(p, mt.first + threadIdx.x, B, ep[threadIdx.x], ep[threadIdx.x], spread);
-    tile_part_sum(p, tix, mt.count, ep);
-    if (spread && tb.fits) spread_flush(tb, ncell, L, L3, acc, H0);
+    if (spread) spread_tile(p, tb, &mrec[0][0], kRecForce, dinc, acc, H0, L3);
+    if (threadIdx.x < 64) {
+        const double r[3] = {B.r[0], B.r[1], B.r[2]};
+        force_epilogue(p, ep_in, r, ep, mrec, spread);
+    }
+    tile_part_sum(p, tix, tb.surface ? 0 : tb.count, ep);
+    if (spread && tb.fits) spread_flush(tb, ncell, L3, acc, H0);
 }
 
-// Force surface variant: the stress integral on the parallel surface at
-// distance force_offset outside the markers (points Y_k = X_k + delta n_k,
-// same normals, areas dSo).  One workgroup per marker tile, as the force
-// kernel: the box of the tile's surface-point stencils (from k_markers) is
-// staged in LDS with rho - 1 and sigma, a row of 16 lanes per marker sums
-// its stencil, one thread per marker forms its parts.  Overwrites the
-// tile's force, torque and pressure-force sums written by the tile kernel.
-__global__ void __launch_bounds__(256) k_offset_force(DevPtrs p, int n_mtiles)
+// The stress integral on the parallel surface at distance force_offset outside
+// the markers (points Y_k = X_k + delta n_k, same normals, areas dSo): the box
+// of the tile's surface-point stencils (from k_markers) is staged in LDS with
+// rho - 1 and sigma, a row of 16 lanes per marker sums its stencil, one thread
+// per marker forms its parts.
+__device__ inline void surface_force_tile(const DevPtrs &p, const TileBox &tb, int tix, unsigned char *lds)
 {
-    __shared__ float box[7][kBoxCells];
-    __shared__ double ev[kTileMarkers][7];
-    __shared__ double tp[kTileMarkers][kPart];
-    const int tix = tile_of_block((int)blockIdx.x, n_mtiles);
-    if (tix >= n_mtiles) return;
-    const MarkerTile mt = p.mtiles[tix];
-    const CaseDev cd = p.cases[mt.c];
-    const BodyView B = body_view(p.body[mt.c]);
-    if (B.err != 0 || !(cd.force_offset > 0.0)) return;
-    const int L = cd.L, L3 = L * L * L;
-    const float *R = p.reg + cd.reg_off * kRegFields;
-    const TileBox tb = p.tbox[n_mtiles + tix];
+    LdsCarve lc{lds};
+    auto &ev = lc.take<double[kTileMarkers][7]>();
+    auto &tp = lc.take<double[kTileMarkers][kPart]>();
+    auto &box = lc.take<float[7][kBoxCells]>();
+    const int L3 = tb.L * tb.L * tb.L;
+    const float *R = p.reg + tb.reg_off * kRegFields;
     const int ncell = tb.e[0] * tb.e[1] * tb.e[2];
+    const BodyDev &B = p.body[tb.c];
+    const int err = B.err;
+    const double r[3] = {B.r[0], B.r[1], B.r[2]};
+    const int j = threadIdx.x >> 4, col = threadIdx.x & 15;
+    const bool on = j < tb.count;
+    const int k = tb.first + (on ? j : 0);
+    const double dl = p.cases[tb.c].force_offset;
+    double Y[3], w[6];   // this column's weights: x, y and the four z levels
+#pragma unroll
+    for (int a = 0; a < 3; a++) Y[a] = p.X[3 * k + a] + dl * p.N[3 * k + a];
     // fields 0 (rho - 1) and 4..9 (sigma xx yy zz xy xz yz)
     if (tb.fits) {
         for (int i = threadIdx.x; i < ncell; i += blockDim.x) {
-            const int q = box_region_cell(i, tb, L);
+            const int q = box_region_cell(i, tb);
             box[0][i] = R[q];
 #pragma unroll
             for (int f = 1; f < 7; f++) box[f][i] = R[(f + 3) * L3 + q];
         }
     }
+    if (err != 0) return;
     __syncthreads();
-    const int j = threadIdx.x >> 4, col = threadIdx.x & 15;
-    const bool on = j < mt.count;
-    const int k = mt.first + (on ? j : 0);
-    const double dl = cd.force_offset;
-    double Y[3], w[12];
+    w[0] = phi4((double)((int)floor(Y[0]) - 1 + (col & 3)) - Y[0]);
+    w[1] = phi4((double)((int)floor(Y[1]) - 1 + (col >> 2)) - Y[1]);
 #pragma unroll
-    for (int a = 0; a < 3; a++) Y[a] = p.X[3 * k + a] + dl * p.N[3 * k + a];
-#pragma unroll
-    for (int d = 0; d < 3; d++) {
-        const int n0 = (int)floor(Y[d]) - 1;
-#pragma unroll
-        for (int o = 0; o < 4; o++) w[4 * d + o] = phi4((double)(n0 + o) - Y[d]);
-    }
-    const Column cn = column_nodes(Y, w, col, tb, cd, B);
+    for (int z = 0; z < 4; z++) w[2 + z] = phi4((double)((int)floor(Y[2]) - 1 + z) - Y[2]);
+    const Column cn = column_nodes(p, Y, w[0], w[1], w + 2, col, tb);
     double v[7];
 #pragma unroll
     for (int f = 0; f < 7; f++) v[f] = 0.0;
@@ -972,8 +1069,8 @@ __global__ void __launch_bounds__(256) k_offset_force(DevPtrs p, int n_mtiles)
 #pragma unroll
         for (int f = 0; f < 7; f++) ev[j][f] = v[f];
     __syncthreads();
-    if ((int)threadIdx.x < mt.count) {
-        const int m = mt.first + threadIdx.x;
+    if ((int)threadIdx.x < tb.count) {
+        const int m = tb.first + threadIdx.x;
         const double *e = ev[threadIdx.x];
         const double nk[3] = {p.N[3 * m], p.N[3 * m + 1], p.N[3 * m + 2]};
         const double pr = (double)CS2 * e[0];
@@ -982,7 +1079,7 @@ __global__ void __launch_bounds__(256) k_offset_force(DevPtrs p, int n_mtiles)
 #pragma unroll
         for (int a = 0; a < 3; a++) {
             s[a] = sg[a][0] * nk[0] + sg[a][1] * nk[1] + sg[a][2] * nk[2];
-            rel[a] = p.X[3 * m + a] + dl * nk[a] - B.r[a];
+            rel[a] = p.X[3 * m + a] + dl * nk[a] - r[a];
         }
         cross3(rel, s, ts);
         const double dA = p.dSo[m];
@@ -993,51 +1090,67 @@ __global__ void __launch_bounds__(256) k_offset_force(DevPtrs p, int n_mtiles)
             tp[threadIdx.x][6 + a] = dA * (-pr) * nk[a];
         }
     }
-    tile_part_sum(p, tix, mt.count, tp);
+    tile_part_sum(p, tix, tb.count, tp);
+}
+
+__global__ void __launch_bounds__(256) EIGHT_WAVES k_interp_force_tiles(DevPtrs p, int n_mtiles, int spread)
+{
+    extern __shared__ __align__(16) unsigned char lds_dyn[];
+    const int tix = tile_of_block((int)blockIdx.x, n_mtiles);
+    if (tix >= n_mtiles) return;
+    const TileBox tb = p.tbox[tix];
+    force_tile(p, tb, tix, spread, lds_dyn);
+}
+
+__global__ void __launch_bounds__(256) EIGHT_WAVES k_surface_force_tiles(DevPtrs p, int n_mtiles)
+{
+    extern __shared__ __align__(16) unsigned char lds_dyn[];
+    const int tix = tile_of_block((int)blockIdx.x, n_mtiles);
+    if (tix >= n_mtiles) return;
+    const TileBox tb = p.tbox[n_mtiles + tix];
+    if (tb.surface) surface_force_tile(p, tb, tix, lds_dyn);
 }
 
 // Spreading of the increments dh over a tile into accumulator 0 (H += S[dh],
 // h_k += dh): LDS accumulation, then one HBM atomic per touched cell.  With
 // masked set, cases whose sequence has ended are skipped.
-__global__ void __launch_bounds__(256) k_spread_tiles(DevPtrs p, int n_mtiles, int masked)
+__global__ void __launch_bounds__(256) EIGHT_WAVES k_spread_tiles(DevPtrs p, int n_mtiles, int masked)
 {
     __shared__ unsigned long long acc[3][kBoxCells];
     __shared__ double mrec[kTileMarkers][kRecForce];   // the tile's marker records
     __shared__ double dinc[kTileMarkers][3];           // the increments dh to spread
     const int tix = tile_of_block((int)blockIdx.x, n_mtiles);
     if (tix >= n_mtiles) return;
-    const MarkerTile mt = p.mtiles[tix];
-    const CaseDev cd = p.cases[mt.c];
-    const BodyView B = body_view(p.body[mt.c]);
-    if (B.err != 0 || (masked && !B.active)) return;
-    const int L = cd.L, L3 = L * L * L;
-    long long *H = p.H + cd.reg_off * 3;
     const TileBox tb = p.tbox[tix];
+    const int err = p.body[tb.c].err, active = p.body[tb.c].active;
+    const int L3 = tb.L * tb.L * tb.L;
+    long long *H = p.H + tb.reg_off * 3;
     const int ncell = tb.e[0] * tb.e[1] * tb.e[2];
     RecordLoad<kRecForce> rl;
-    rl.load(p, mt);
+    rl.load(p, tb);
     // thread j < count: marker j's increment, and h_k += dh
     const int t = threadIdx.x;
     double dh[3] = {0.0, 0.0, 0.0}, hk[3] = {0.0, 0.0, 0.0};
-    if (t < mt.count)
+    if (t < tb.count)
 #pragma unroll
         for (int a = 0; a < 3; a++) {
-            dh[a] = p.dh[3 * (mt.first + t) + a];
-            hk[a] = p.hk[3 * (mt.first + t) + a];
+            dh[a] = p.dh[3 * (tb.first + t) + a];
+            hk[a] = p.hk[3 * (tb.first + t) + a];
         }
+    if (err != 0 || (masked && !active)) return;
     if (tb.fits)
         for (int i = threadIdx.x; i < ncell; i += blockDim.x) acc[0][i] = acc[1][i] = acc[2][i] = 0ull;
-    rl.store(mt, mrec);
-    if (t < mt.count)
+    rl.store(tb, mrec);
+    if (t < tb.count)
 #pragma unroll
         for (int a = 0; a < 3; a++) {
             dinc[t][a] = dh[a];
-            p.hk[3 * (mt.first + t) + a] = hk[a] + dh[a];
+            p.hk[3 * (tb.first + t) + a] = hk[a] + dh[a];
         }
     __syncthreads();
-    spread_tile(p, mt, tb, cd, B, &mrec[0][0], kRecForce, dinc, acc, H, L3);
+    spread_tile(p, tb, &mrec[0][0], kRecForce, dinc, acc, H, L3);
     __syncthreads();
-    if (tb.fits) spread_flush(tb, ncell, L, L3, acc, H);
+    if (tb.fits) spread_flush(tb, ncell, L3, acc, H);
 }
 
 // Interpolation of u* + H over a tile (staged in LDS, FP64; H the sum of
@@ -1046,9 +1159,8 @@ __global__ void __launch_bounds__(256) k_spread_tiles(DevPtrs p, int n_mtiles, i
 // With spread_to >= 0 the same pass spreads dh (the next cycle's spread,
 // h_k += dh) into accumulator spread_to, which no interpolation of this
 // pass reads.
-template <int NB, int MINW>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MINW, MINW == 8 ? 8 : lds_waves(kLdsUpdate))))
-k_interp_update_tiles(DevPtrs p, int n_mtiles, int masked, int spread_to, int ft_total)
+template <int NB>
+__global__ void __launch_bounds__(256) EIGHT_WAVES k_interp_update_tiles(DevPtrs p, int n_mtiles, int masked, int spread_to, int ft_total)
 {
     extern __shared__ __align__(16) unsigned char lds_dyn[];
     LdsCarve lc{lds_dyn};
@@ -1059,15 +1171,17 @@ k_interp_update_tiles(DevPtrs p, int n_mtiles, int masked, int spread_to, int ft
     auto &rmax = lc.take<double[kTileMarkers]>();
     const int tix = tile_of_block((int)blockIdx.x, n_mtiles);
     if (tix >= n_mtiles) return;
-    const MarkerTile mt = p.mtiles[tix];
-    const CaseDev cd = p.cases[mt.c];
-    const BodyView B = body_view(p.body[mt.c]);
-    if (B.err != 0 || (masked && !B.active)) return;
-    const int L = cd.L, L3 = L * L * L;
-    const float *R = p.reg + cd.reg_off * kRegFields;
-    const long long *H = p.H + cd.reg_off * 3;
-    long long *Hs = p.H + (spread_to > 0 ? spread_to : 0) * p.hstride + cd.reg_off * 3;
+    if (NB == 1 && blockIdx.y == 1) {
+        const TileBox ts = p.tbox[n_mtiles + tix];
+        if (ts.surface) surface_force_tile(p, ts, tix, lds_dyn);
+        return;
+    }
     const TileBox tb = p.tbox[tix];
+    const int err = p.body[tb.c].err, active = p.body[tb.c].active;
+    const int L3 = tb.L * tb.L * tb.L;
+    const float *R = p.reg + tb.reg_off * kRegFields;
+    const long long *H = p.H + tb.reg_off * 3;
+    long long *Hs = p.H + (spread_to > 0 ? spread_to : 0) * p.hstride + tb.reg_off * 3;
     const int ncell = tb.e[0] * tb.e[1] * tb.e[2];
     // H at region cell q and component a: the exact integer sum of the accumulators
     const long long hstride = p.hstride;
@@ -1079,10 +1193,10 @@ k_interp_update_tiles(DevPtrs p, int n_mtiles, int masked, int spread_to, int ft
     };
     // the markers' records load in the same round as the box
     RecordLoad<kRecUpdate> rl;
-    rl.load(p, mt);
+    rl.load(p, tb);
     if (tb.fits) {
         for (int i = threadIdx.x; i < ncell; i += blockDim.x) {
-            const int q = box_region_cell(i, tb, L);
+            const int q = box_region_cell(i, tb);
 #pragma unroll
             for (int a = 0; a < 3; a++) {
                 box[a][i] = (double)R[(1 + a) * L3 + q] + (double)h_at(a, q) * kFixInv;
@@ -1090,14 +1204,16 @@ k_interp_update_tiles(DevPtrs p, int n_mtiles, int masked, int spread_to, int ft
             }
         }
     }
-    rl.store(mt, mrec);
+    if (err != 0 || (masked && !active)) return;
+    rl.store(tb, mrec);
     __syncthreads();
     // rows past the tile's markers repeat marker 0 and store nothing
     const int j = threadIdx.x >> 4, col = threadIdx.x & 15;
-    const bool on = j < mt.count;
+    const bool on = j < tb.count;
     const double *rc = mrec[on ? j : 0];
     const double X[3] = {rc[0], rc[1], rc[2]};
-    const Column cn = column_nodes(X, rc + kRecW, col, tb, cd, B);
+    const double *wr = rc + kRecW;   // 4 weights per axis
+    const Column cn = column_nodes(p, X, wr[col & 3], wr[4 + (col >> 2)], wr + 8, col, tb);
     double v[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int z = 0; z < 4; z++) {
@@ -1115,7 +1231,7 @@ k_interp_update_tiles(DevPtrs p, int n_mtiles, int masked, int spread_to, int ft
     for (int a = 0; a < 3; a++) v[a] = row_sum(v[a]);
     const double e[3] = {rc[3] - v[0], rc[4] - v[1], rc[5] - v[2]};
     if (on && col == 0) {
-        const int k = mt.first + j;
+        const int k = tb.first + j;
         double res = 0.0;
 #pragma unroll
         for (int a = 0; a < 3; a++) {
@@ -1127,17 +1243,17 @@ k_interp_update_tiles(DevPtrs p, int n_mtiles, int masked, int spread_to, int ft
         rmax[j] = res;
     }
     __syncthreads();
-    if (spread_to >= 0) spread_tile(p, mt, tb, cd, B, &mrec[0][0], kRecUpdate, dinc, acc, Hs, L3);
+    if (spread_to >= 0) spread_tile(p, tb, &mrec[0][0], kRecUpdate, dinc, acc, Hs, L3);
     __syncthreads();
     if (threadIdx.x == 0) {
         double m = 0.0;
-        for (int t = 0; t < mt.count; t++) m = fmax(m, rmax[t]);
+        for (int t = 0; t < tb.count; t++) m = fmax(m, rmax[t]);
         p.res[tix] = m;
     }
-    if (spread_to >= 0 && tb.fits) spread_flush(tb, ncell, L, L3, acc, Hs);
+    if (spread_to >= 0 && tb.fits) spread_flush(tb, ncell, L3, acc, Hs);
     // the case's force totals from the force kernels' tile parts (complete at
     // this kernel's start), formed by the workgroup of its first tile
-    if (ft_total && tix == cd.tile_off) case_force_total(p, cd, p.body[mt.c]);
+    if (ft_total && tix == tb.tile_off) case_force_total(p, p.cases[tb.c], p.body[tb.c]);
 }
 
 // FP64 force, torque and pressure-force totals of each case from its tile
@@ -1520,25 +1636,29 @@ static hipError_t ibm_impl(const void *prev, void *cur, const DevPtrs &p, int n_
         int L = 1;
         while ((long long)L * L * L < maxL3) L++;
         const long long E3 = (long long)(L + 2) * (L + 2) * (L + 2);
-        hipLaunchKernelGGL(k_region_expand_mom, dim3((unsigned)((E3 + 255) / 256), n_cases), blk, 0, s, (const T *)prev, p);
+        hipLaunchKernelGGL(k_region_expand_mom, dim3((unsigned)((E3 + 255) / 256), n_cases), blk, 0, s,
+                           (const T *)prev, p);
     }
     hipLaunchKernelGGL(k_region_gather<CD>, reg_grid, blk, 0, s, (const T *)prev, p, prev_id);
     // plain start with at most kHBufs cycles: each cycle's spread rides on
     // the pass before it (force + spread 1, update c + spread c + 1)
     static_assert(kHBufs == 4, "the launch below instantiates 1..4 accumulators");
-    constexpr int W = 8;   // register budget of the tile passes
     const int fused = ibm_fused(warm_mode, cycles);
-    hipLaunchKernelGGL(k_interp_force_tiles<W>, tile_grid, blk, kLdsForce, s, p, n_mtiles, fused);
-    if (force_surface) hipLaunchKernelGGL(k_offset_force, tile_grid, blk, 0, s, p, n_mtiles);
-    // the fused sequence forms the force totals in its first update pass
-    if (!fused) hipLaunchKernelGGL(k_reduce_ft, dim3(n_cases), blk, 0, s, p);
+    hipLaunchKernelGGL(k_interp_force_tiles, tile_grid, blk, kLdsForce, s, p, n_mtiles, fused);
+    // the fused sequence takes the force surface beside its first update pass
+    // (both need the gathered region alone of what the force kernel leaves) and
+    // forms the force totals in its second
+    if (!fused || cycles < 2) {
+        if (force_surface) hipLaunchKernelGGL(k_surface_force_tiles, tile_grid, blk, kLdsSurface, s, p, n_mtiles);
+        hipLaunchKernelGGL(k_reduce_ft, dim3(n_cases), blk, 0, s, p);
+    }
     // one sequence of multi-direct forcing cycles (Sec. 2.2, l = 1..4): spread
     // the increment, then interpolate and form the next increment; the
     // residual after the last spread is the sequence's residual
     auto sequence = [&](int ncyc, int slot0, int masked) {
         for (int cyc = 1; cyc <= ncyc; cyc++) {
             hipLaunchKernelGGL(k_spread_tiles, tile_grid, blk, 0, s, p, n_mtiles, masked);
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_interp_update_tiles<1, W>), tile_grid, blk, kLdsUpdate, s, p, n_mtiles, masked, -1, 0);
+            hipLaunchKernelGGL(k_interp_update_tiles<1>, tile_grid, blk, kLdsUpdate, s, p, n_mtiles, masked, -1, 0);
             if (diag || cyc == ncyc)
                 hipLaunchKernelGGL(k_reduce_resid, dim3(n_cases), blk, 0, s, p, slot0 + cyc - 1, masked, 0);
         }
@@ -1546,15 +1666,16 @@ static hipError_t ibm_impl(const void *prev, void *cur, const DevPtrs &p, int n_
     if (fused) {
         for (int cyc = 1; cyc <= cycles; cyc++) {
             const int to = cyc < cycles ? cyc : -1;
-            // the first pass forms the force totals; the last pass's residual
+            // the second pass forms the force totals; the last pass's residual
             // is reduced by the forced correction (or, with diag, every
             // cycle's by its own kernel)
-            const int ft = cyc == 1;
+            const int ft = cyc == 2;
+            const dim3 first(tile_grid.x, force_surface && cycles >= 2 ? 2 : 1);
             switch (cyc) {
-            case 1: hipLaunchKernelGGL(HIP_KERNEL_NAME(k_interp_update_tiles<1, W>), tile_grid, blk, kLdsUpdate, s, p, n_mtiles, 0, to, ft); break;
-            case 2: hipLaunchKernelGGL(HIP_KERNEL_NAME(k_interp_update_tiles<2, W>), tile_grid, blk, kLdsUpdate, s, p, n_mtiles, 0, to, ft); break;
-            case 3: hipLaunchKernelGGL(HIP_KERNEL_NAME(k_interp_update_tiles<3, W>), tile_grid, blk, kLdsUpdate, s, p, n_mtiles, 0, to, ft); break;
-            default: hipLaunchKernelGGL(HIP_KERNEL_NAME(k_interp_update_tiles<4, W>), tile_grid, blk, kLdsUpdate, s, p, n_mtiles, 0, to, ft); break;
+            case 1: hipLaunchKernelGGL(k_interp_update_tiles<1>, first, blk, kLdsUpdate, s, p, n_mtiles, 0, to, ft); break;
+            case 2: hipLaunchKernelGGL(k_interp_update_tiles<2>, tile_grid, blk, kLdsUpdate, s, p, n_mtiles, 0, to, ft); break;
+            case 3: hipLaunchKernelGGL(k_interp_update_tiles<3>, tile_grid, blk, kLdsUpdate, s, p, n_mtiles, 0, to, ft); break;
+            default: hipLaunchKernelGGL(k_interp_update_tiles<4>, tile_grid, blk, kLdsUpdate, s, p, n_mtiles, 0, to, ft); break;
             }
             if (diag)
                 hipLaunchKernelGGL(k_reduce_resid, dim3(n_cases), blk, 0, s, p, cyc - 1, 0, 0);
@@ -1575,7 +1696,7 @@ static hipError_t ibm_impl(const void *prev, void *cur, const DevPtrs &p, int n_
         hipLaunchKernelGGL(k_gate_begin, case_grid, case_blk, 0, s, p, n_cases);
         for (int cyc = 1; cyc <= warm_cycles; cyc++) {
             hipLaunchKernelGGL(k_spread_tiles, tile_grid, blk, 0, s, p, n_mtiles, 1);
-            hipLaunchKernelGGL(HIP_KERNEL_NAME(k_interp_update_tiles<1, W>), tile_grid, blk, kLdsUpdate, s, p, n_mtiles, 1, -1, 0);
+            hipLaunchKernelGGL(k_interp_update_tiles<1>, tile_grid, blk, kLdsUpdate, s, p, n_mtiles, 1, -1, 0);
             hipLaunchKernelGGL(k_reduce_resid, dim3(n_cases), blk, 0, s, p, cyc - 1, 1, cyc);
         }
         hipLaunchKernelGGL(k_gate, case_grid, case_blk, 0, s, p, n_cases);
