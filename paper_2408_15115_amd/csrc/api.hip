@@ -157,10 +157,14 @@ void build_moment_tiles(Plan &P)
 // (measured, one step of the lattice kernel alone):
 //   - both population buffers together fit the 256 MB memory-side cache: the
 //     hint sends the data past it.  FP32, 131 x 77 x 93: 47 us with the hint,
-//     36 without; 104^3 (242 MB): 47 and 41; 110^3 (288 MB): 55 and 57.  With
-//     2-byte elements the two are within 5 % up to there, either way, so that
-//     form keeps the hint; moment storage below 64 MB too (64^3: 13.8 and 14.4;
-//     112^3: 41 and 36);
+//     36 without; 104^3 (242 MB): 47 and 41; 110^3 (288 MB): 55 and 57.  Up to
+//     40 MB the hint is the better one again, as the ordinary form's lines are
+//     written back from the L2s when the kernel ends: FP32 48^3: 8.7 and 9.7,
+//     56^3 (38 MB): 9.8 and 11.6, 60^3 (47 MB): 13.0 and 12.3; D3Q19 56^3
+//     (27 MB): 7.7 and 8.9, 64^3 (40 MB): 9.0 and 9.0, 72^3: 14.4 and 12.7.
+//     With 2-byte elements the two are within 5 % up to there, either way, so
+//     that form keeps the hint; moment storage below 64 MB too (64^3: 13.8 and
+//     14.4; 112^3: 41 and 36);
 //   - moment storage, whose step writes row by row, in boxes whose rows are
 //     not whole 64-cell wavefronts: the hint writes the lines that two rows
 //     share in parts.  160 x 160 x 480: 308 and 244 us; 250 x 250 x 760: 1233
@@ -173,7 +177,7 @@ void store_policy(Plan &P, int storage)
     long long whole = 0, ragged = 0;
     for (const CaseDev &d : P.cd) (d.nx % 64 != 0 ? ragged : whole) += d.cells;
     P.keep = storage == LBM_MOM ? bytes >= kCache / 4 && (bytes <= kCache || ragged > whole)
-                                : storage == LBM_F32 && bytes <= kCache;
+                                : storage == LBM_F32 && bytes >= (40LL << 20) && bytes <= kCache;
 }
 
 // Marker order and tiles of one case: sort the markers along a Morton curve

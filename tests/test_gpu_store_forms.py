@@ -60,3 +60,20 @@ def test_d3q19_beyond_the_cache_matches_oracle(T, orc):
     S.close()
     ref = np.moveaxis(orc.collide_grid19(orc.stream19(C), tau), -1, 0)
     assert max_rel(gpu, ref) < 1e-5
+
+
+@pytest.mark.parametrize("lattice,nx,ny,nz", [(27, 62, 61, 60), (19, 72, 66, 65)])
+def test_boxes_that_the_cache_holds_match_oracle(T, orc, lattice, nx, ny, nz):
+    """FP32 buffers past the L2s that the memory-side cache still holds: their
+    stores are ordinary ones."""
+    tau = 0.7
+    rnd, collide, stream = ((W.random_populations, orc.collide_grid, orc.stream_grid) if lattice == 27 else
+                            (W.random_populations19, orc.collide_grid19, orc.stream19))
+    C = collide(rnd(9, nx, ny, nz), tau)
+    S = T.Solver([W.make_case(nx, ny, nz, tau, W.BC_PERIODIC, W.BC_PERIODIC)], lattice=lattice)
+    S.set_populations(np.ascontiguousarray(np.moveaxis(C, -1, 0)))
+    S.lbm_step()
+    gpu = S.populations()
+    S.close()
+    ref = np.moveaxis(collide(stream(C), tau), -1, 0)
+    assert max_rel(gpu, ref) < 1e-5
