@@ -39,7 +39,7 @@ struct Plan {
     long long pop_elems = 0, reg_cells = 0;
     size_t off_cases, off_body, off_tiles, off_counter, off_mcase, off_xb, off_nb, off_dS, off_X, off_N, off_U, off_hk,
         off_dh, off_part, off_res, off_reg, off_H, off_feat, off_h0, off_hk2, off_hs, off_dSo, off_mtiles, off_tbox, off_log,
-        off_mark, off_mark2, off_xmark, off_wt, off_dsh, off_rpop, off_fine0, off_fine1, aux_bytes;
+        off_mark, off_mark2, off_xmark, off_geo, off_wt, off_dsh, off_rpop, off_fine0, off_fine1, aux_bytes;
     long long xreg_cells = 0;   // moment storage: cells of all expanded regions (edge L + 2)
     long long fine_elems = 0;   // FP16/BF16 storage: floats of all full-precision boxes (per buffer)
     long long max_box = 0;      // cells of the largest box
@@ -360,6 +360,7 @@ std::string make_plan(const lbm_case *cases, const lbm_body *bodies, int n, cons
     P.off_reg = take(sizeof(float) * kRegFields * std::max<long long>(reg, 1));
     P.off_H = take(sizeof(long long) * 3 * kHBufs * std::max<long long>(reg, 1));
     P.off_mark = take((size_t)std::max<long long>(reg, 1));
+    P.off_geo = take(sizeof(StepGeometry) * (size_t)P.cd.size());
     P.off_mark2 = take((size_t)std::max<long long>(reg, 1));
     P.off_xmark = take((size_t)std::max<long long>(mom ? P.xreg_cells : 0, 1));
     P.off_feat = take(sizeof(float) * kMlpIn * M);
@@ -600,6 +601,7 @@ int32_t lbm_init(const lbm_case *cases, const lbm_body *bodies, int32_t n_cases,
     p.H = (long long *)(a + P.off_H);
     p.hstride = 3 * std::max<long long>(P.reg_cells, 1);
     p.mark = (unsigned char *)(a + P.off_mark);
+    p.geo = (StepGeometry *)(a + P.off_geo);
     p.mark2 = (unsigned char *)(a + P.off_mark2);
     p.xmark = ctx->opt.storage == LBM_MOM ? (unsigned char *)(a + P.off_xmark) : nullptr;
     p.wt = (double *)(a + P.off_wt);
@@ -755,7 +757,8 @@ static int32_t do_lbm_step(lbm_ctx *ctx)
     return LBM_OK;
 }
 
-static int32_t do_ibm(lbm_ctx *ctx)
+// tail: see launch_correct
+static int32_t do_ibm(lbm_ctx *ctx, int tail = 0)
 {
     if (!ctx->has_body) return LBM_OK;
     const bool serial = ctx->opt.serial_ibm != 0;
@@ -773,18 +776,16 @@ static int32_t do_ibm(lbm_ctx *ctx)
     const int resid_slot =
         ibm_fused(ctx->warm_mode, ctx->opt.ibm_cycles) && !ctx->opt.ibm_diag ? ctx->opt.ibm_cycles - 1 : -1;
     HIPCHK(ctx, launch_correct(ctx->opt.storage, ctx->pop[ctx->cur], ctx->p, ctx->n, ctx->plan.Mtot, ctx->plan.maxL3,
-                               ctx->cur, resid_slot, ctx->stream),
+                               ctx->cur, resid_slot, tail, ctx->stream),
            "forced correction");
     ctx->needs_ibm = false;
     return LBM_OK;
 }
 
-// advance set: the next step's body advance rides in the window test's kernel
-static int32_t do_window(lbm_ctx *ctx, int advance = 0)
+static int32_t do_window(lbm_ctx *ctx)
 {
     if (!ctx->has_body) return LBM_OK;
-    HIPCHK(ctx, launch_window(ctx->opt.storage, ctx->pop[ctx->cur], ctx->p, ctx->n, ctx->plan.max_slab, ctx->cur,
-                              advance, ctx->stream),
+    HIPCHK(ctx, launch_window(ctx->opt.storage, ctx->pop[ctx->cur], ctx->p, ctx->n, ctx->plan.max_slab, ctx->cur, ctx->stream),
            "window_shift");
     return LBM_OK;
 }
@@ -817,15 +818,15 @@ int32_t window_shift(lbm_ctx *ctx)
     return do_window(ctx);
 }
 
-// nsteps whole steps in Table 1 order; between two of them the window test
-// of one and the body advance of the next share a kernel.
+// nsteps whole steps in Table 1 order; the end of each step, and between two
+// of them the body advance, ride in the correction's launch.
 static int32_t run_steps(lbm_ctx *ctx, int nsteps)
 {
     if (nsteps <= 0) return LBM_OK;
     int32_t r = do_body_advance(ctx);
     for (int s = 0; s < nsteps && r == LBM_OK; s++) {
-        if ((r = do_lbm_step(ctx)) || (r = do_ibm(ctx))) return r;
-        r = do_window(ctx, s + 1 < nsteps);
+        if ((r = do_lbm_step(ctx))) return r;
+        r = do_ibm(ctx, s + 1 < nsteps ? 2 : 1);
     }
     return r;
 }

@@ -63,6 +63,15 @@ struct BodyDev {
                      // 4: non-finite density or |u| > 0.5.  Nonzero masks (freezes) the case.
 };
 
+// What the forced correction needs of the body, copied by k_markers every step:
+// the correction's launch may move the body on at the same time.
+struct StepGeometry {
+    int org[3], z0;
+    int fo[2][3], fvalid[2];
+    int shift;       // 1: the window test at the end of this step will move the window
+    int pad;
+};
+
 struct Tile {
     int c;           // case
     int first;       // first cell (flat index inside the case) of the tile
@@ -117,6 +126,7 @@ constexpr int kRegFields = 10;
 
 struct DevPtrs {
     CaseDev *cases;
+    StepGeometry *geo;
     BodyDev *body;
     Tile *tiles;
     int *mcase;
@@ -194,16 +204,16 @@ hipError_t launch_ibm(int storage, const void *prev, void *cur, const DevPtrs &p
 // resid_slot >= 0: the correction also forms the case residual of the plain
 // fused forcing sequence (whose last pass leaves the tile maxima) into
 // resid and resid_hist[resid_slot].
+// tail 1: the correction's launch also ends the step (the window test and reset
+// and the step's record); 2: and advances the bodies for the next step.
 hipError_t launch_correct(int storage, void *cur, const DevPtrs &p, int n_cases, int Mtot, int maxL3, int cur_id,
-                          int resid_slot, hipStream_t s);
+                          int resid_slot, int tail, hipStream_t s);
 // Whether the plain forcing sequence runs fused (each spread in the preceding
 // interpolation pass); it then leaves its residual to the correction.
 inline bool ibm_fused(int warm_mode, int cycles) { return warm_mode == 0 && cycles <= kHBufs; }
 hipError_t launch_targets(const DevPtrs &p, int Mtot, float *out, hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, long long bytes, hipStream_t s);
-// The window test and reset of Sec. 2.5; with advance set, the test and the
-// next step's body advance run in one kernel (identical results).
-hipError_t launch_window(int storage, void *cur, const DevPtrs &p, int n_cases, int max_slab, int cur_id, int advance,
-                         hipStream_t s);
+// The window test and reset of Sec. 2.5 and the step's record.
+hipError_t launch_window(int storage, void *cur, const DevPtrs &p, int n_cases, int max_slab, int cur_id, hipStream_t s);
 
 }  // namespace turret

@@ -165,6 +165,12 @@ __device__ inline BodyView body_view(const BodyDev &B)
     return v;
 }
 
+// The window test of Sec. 2.5 at the body's height rz.
+__device__ inline bool window_shifts(const CaseDev &cd, double rz)
+{
+    return cd.M > 0 && cd.dz > 0 && cd.h_end > 0.0 && rz < cd.h_end;
+}
+
 // Moment storage: the tag that selects the moment forms of the region gather,
 // the correction and the window reset.
 struct CodecMom {
@@ -617,6 +623,19 @@ __global__ void __launch_bounds__(64) EIGHT_WAVES k_markers(DevPtrs p, int n_mti
     const BodyView B = body_view(Bd);
     if (B.err != 0) return;
     const int lane = threadIdx.x;
+    if (tix == cd.tile_off && lane == 0) {   // the step's geometry, for the correction
+        StepGeometry &G = p.geo[mt.c];
+        G.z0 = Bd.z0;
+        G.shift = window_shifts(cd, B.r[2]);
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            G.org[a] = B.org[a];
+            G.fo[0][a] = Bd.fo[0][a];
+            G.fo[1][a] = Bd.fo[1][a];
+        }
+        G.fvalid[0] = Bd.fvalid[0];
+        G.fvalid[1] = Bd.fvalid[1];
+    }
     const bool on = lane < mt.count;
     const int k = mt.first + (on ? lane : 0);
     const double xb[3] = {p.xb[3 * k], p.xb[3 * k + 1], p.xb[3 * k + 2]};
@@ -1364,31 +1383,154 @@ __global__ void k_targets(DevPtrs p, int Mtot, float *out)
     for (int a = 0; a < 3; a++) out[3 * k + a] = (float)(p.hk[3 * k + a] / p.hs[k] - (double)ft[kFeatHPrev + a]);
 }
 
+// ----------------------------------------------------------------- window
+// Sec. 2.5: below h_end the content and the body move up by dz rows.  With
+// the ring layout the move is the origin change z0 -> z0 - dz; the dz rows
+// that now form the bottom (the former top rows) restart at rest.
+// The step's record for the case's log ring, taken after the window test.
+struct StepRecord {
+    double v[kLogFields];
+};
+
+__device__ inline StepRecord window_trigger_case(const DevPtrs &p, int c)
+{
+    const CaseDev &cd = p.cases[c];
+    BodyDev &B = p.body[c];
+    const int dz = cd.dz, nz = cd.nz;
+    const double rz = B.r[2];
+    const bool shift = B.err == 0 && window_shifts(cd, rz);
+    B.shift_now = 0;
+    if (shift) {
+        B.r[2] = rz + (double)dz;
+        B.z0 = wrapi(B.z0 - dz, nz);
+        B.fo[0][2] += dz;   // the full-precision boxes move with the content
+        B.fo[1][2] += dz;
+        B.shift_now = 1;
+        B.shifts += 1;
+    }
+    StepRecord rec;
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        rec.v[a] = B.r[a];
+        rec.v[12 + a] = B.v[a];
+        rec.v[15 + a] = B.w[a];
+        rec.v[18 + a] = B.F[a];
+        rec.v[21 + a] = B.T[a];
+        rec.v[24 + a] = B.Fp[a];
+    }
+#pragma unroll
+    for (int a = 0; a < 9; a++) rec.v[3 + a] = B.d[a];
+    rec.v[27] = B.resid;
+    rec.v[28] = B.steps;
+    rec.v[29] = B.shifts;
+    rec.v[30] = B.z0;
+    rec.v[31] = B.err;
+    return rec;
+}
+
+// Appends a record to the case's log ring.  Written last in its kernel: the
+// stores go through a plain double pointer, which the compiler must assume
+// may alias the body state, so no body field is read after them.
+__device__ inline void log_append(const DevPtrs &p, int c, const StepRecord &rec)
+{
+    BodyDev &B = p.body[c];
+    const unsigned int n = B.logged;
+    B.logged = n + 1;
+    double *dst = p.log + ((long long)c * kLogCap + n % kLogCap) * kLogFields;
+#pragma unroll
+    for (int k = 0; k < kLogFields; k++) dst[k] = rec.v[k];
+}
+
+// The re-injected rows to rest, by thread t of nt: ring origin z0 and
+// full-precision box origin fo after the shift.
+template <class CD>
+__device__ inline void reset_rows(typename CD::T *cur, const DevPtrs &p, const CaseDev &cd, int z0, const int fo[3],
+                                  int fvalid, int cid, int t, int nt)
+{
+    const int slab = cd.nx * cd.ny;
+    for (int idx = t; idx < cd.dz * slab; idx += nt) {
+        const int zrow = idx / slab, rem = idx - zrow * slab;
+        int zc = zrow + z0;
+        if (zc >= cd.nz) zc -= cd.nz;
+        typename CD::T *dst = cur + cd.pop_off + (long long)zc * slab + rem;
+        if constexpr (std::is_same<CD, CodecMom>::value) {
+#pragma unroll
+            for (int k = 0; k < 10; k++) dst[(long long)k * cd.plane] = 0.0f;   // the rest state's moments
+        } else {
+            Unroll<0, Q>::run([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                dst[(long long)i * cd.plane] = CD::template enc<i>(0.0f);
+            });
+            if (cd.LB[0] > 0 && fvalid) {
+                const int slot = fine_slot(cd, fo, rem % cd.nx, rem / cd.nx, zrow);
+                if (slot >= 0) {
+                    float *F = p.fine[cid] + cd.fine_off;
+                    const long long fplane = fine_plane(cd);
+#pragma unroll
+                    for (int i = 0; i < Q; i++) F[(long long)i * fplane + slot] = 0.0f;
+                }
+            }
+        }
+    }
+}
+
+// The end of a step, one workgroup per case, in the correction's launch: the
+// forcing sequence's residual (its tile maxima are complete there) and, for
+// steps that the library sequences itself (lbm_run, graph capture), the window
+// test, the step's record and (TAIL_ADVANCE) the next step's body advance.  The
+// correction's other workgroups, which take place at the same time, read the
+// body's geometry from the copy that k_markers left (StepGeometry) and reset
+// the re-injected rows.  The window test, the reset and the launches between
+// them took 14 us at the end of every step; here they take none beside the
+// correction.
+enum { TAIL_NONE, TAIL_WINDOW, TAIL_ADVANCE };
+
+__device__ inline void step_end(const DevPtrs &p, int c, bool live, int resid_slot, int tail)
+{
+    if (live && resid_slot >= 0) case_resid_total(p, p.cases[c], p.body[c], resid_slot);
+    if (tail == TAIL_NONE || threadIdx.x != 0) return;
+    const StepRecord rec = window_trigger_case(p, c);
+    if (tail == TAIL_ADVANCE) body_advance_case(p, c);
+    log_append(p, c, rec);
+}
+
 // Forced collision of Sec. 2.2: the lattice kernel wrote
 // f0(rho, u) + (1 - 1/tau) f1; cells carrying an immersed force get
 // f0(rho, u + tau h) - f0(rho, u) added (in the momentum-exact variant less
 // the first-order term w_i xi_i . (tau - 1) rho h / cs^2).  Only cells
 // marked this step can carry a force; their marks are cleared here.
 template <class CD>
-__global__ void k_correct(typename CD::T *__restrict__ cur, DevPtrs p, int did, int resid_slot)
+__global__ void __launch_bounds__(256) k_correct(typename CD::T *__restrict__ cur, DevPtrs p, int did, int resid_slot,
+                                                 int tail)
 {
+    __shared__ ScanList list;
     const int c = blockIdx.y;
-    const CaseDev cd = p.cases[c];
-    const BodyView B = body_view(p.body[c]);
-    if (cd.M == 0 || B.err != 0) return;
-    // the forcing sequence's residual (its tile maxima are complete here)
-    if (resid_slot >= 0 && blockIdx.x == 0) case_resid_total(p, cd, p.body[c], resid_slot);
-    const int L = cd.L, L3 = L * L * L;
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= L3) return;
-    unsigned char &mk = p.mark[cd.reg_off + q];
-    if (!mk) return;
-    mk = 0;
+    const CaseDev &cd = p.cases[c];
+    const bool live = cd.M > 0 && p.body[c].err == 0;
+    if (blockIdx.x == 0) {
+        step_end(p, c, live, resid_slot, tail);
+        return;
+    }
+    if (!live) return;
+    const StepGeometry &G = p.geo[c];
+    const int L = cd.L, L3 = L * L * L, first = (blockIdx.x - 1) * 256;
+    const bool shift = tail && G.shift;
+    if (shift) {
+        const int fo[3] = {G.fo[did][0], G.fo[did][1], G.fo[did][2] + cd.dz};
+        reset_rows<CD>(cur, p, cd, wrapi(G.z0 - cd.dz, cd.nz), fo, G.fvalid[did], did, first + threadIdx.x,
+                       (gridDim.x - 1) * 256);
+    }
+    if (first >= L3) return;
+    unsigned char *mk = p.mark + cd.reg_off;
+    const int i0 = first + threadIdx.x;
+    const int q = scan_cells(list, first, i0 < L3 && mk[i0]);
+    if (q < 0) return;
+    mk[q] = 0;
     const int a = q % L, b = (q / L) % L, cc = q / (L * L);
-    const int gz = B.org[2] + cc;
-    if (gz < 0 || gz >= cd.nz) return;
-    const int gx = wrapi(B.org[0] + a, cd.nx), gy = wrapi(B.org[1] + b, cd.ny);
-    int zc = gz + B.z0;
+    const int gz = G.org[2] + cc;
+    if (gz < 0 || gz >= (shift ? cd.nz - cd.dz : cd.nz)) return;   // (rows at rest from here on are left alone)
+    const int gx = wrapi(G.org[0] + a, cd.nx), gy = wrapi(G.org[1] + b, cd.ny);
+    int zc = gz + G.z0;
     if (zc >= cd.nz) zc -= cd.nz;
     const int off = (zc * cd.ny + gy) * cd.nx + gx;
     typename CD::T *dst = cur + cd.pop_off;
@@ -1409,9 +1551,8 @@ __global__ void k_correct(typename CD::T *__restrict__ cur, DevPtrs p, int did, 
     int slot = -1;
     float *F = nullptr;
     long long fplane = 0;
-    if (cd.LB[0] > 0 && p.body[c].fvalid[did]) {
-        const BodyDev &Bd = p.body[c];
-        const int fo[3] = {Bd.fo[did][0], Bd.fo[did][1], Bd.fo[did][2]};
+    if (cd.LB[0] > 0 && G.fvalid[did]) {
+        const int fo[3] = {G.fo[did][0], G.fo[did][1], G.fo[did][2]};
         slot = fine_slot(cd, fo, gx, gy, gz);
         F = p.fine[did] + cd.fine_off;
         fplane = fine_plane(cd);
@@ -1456,27 +1597,32 @@ __global__ void k_correct(typename CD::T *__restrict__ cur, DevPtrs p, int did, 
 // with lambda = 1, or 1 / tau in the momentum-exact variant (the first-order
 // term then carries rho h).  The box's origin is recorded in ring-slot
 // coordinates, which a window shift leaves in place.  Marks are cleared.
-__global__ void k_correct_mom(DevPtrs p, int resid_slot)
+__global__ void __launch_bounds__(256) k_correct_mom(float *__restrict__ cur, DevPtrs p, int did, int resid_slot, int tail)
 {
     const int c = blockIdx.y;
-    const CaseDev cd = p.cases[c];
-    const BodyView B = body_view(p.body[c]);
-    if (cd.M == 0 || B.err != 0) return;
-    if (resid_slot >= 0 && blockIdx.x == 0) case_resid_total(p, cd, p.body[c], resid_slot);
-    const int L = cd.L, L3 = L * L * L;
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q == 0) {
-        BodyDev &Bw = p.body[c];
-        Bw.dorg[0] = wrapi(B.org[0], cd.nx);
-        Bw.dorg[1] = wrapi(B.org[1], cd.ny);
-        Bw.dorg[2] = wrapi(B.org[2] + B.z0, cd.nz);
-        Bw.dvalid = 1;
+    const CaseDev &cd = p.cases[c];
+    const StepGeometry &G = p.geo[c];
+    const bool live = cd.M > 0 && p.body[c].err == 0;
+    if (blockIdx.x == 0) {
+        if (live && threadIdx.x == 0) {
+            BodyDev &B = p.body[c];
+            B.dorg[0] = wrapi(G.org[0], cd.nx);
+            B.dorg[1] = wrapi(G.org[1], cd.ny);
+            B.dorg[2] = wrapi(G.org[2] + G.z0, cd.nz);
+            B.dvalid = 1;
+        }
+        step_end(p, c, live, resid_slot, tail);
+        return;
     }
+    if (!live) return;
+    const int L = cd.L, L3 = L * L * L, q = (blockIdx.x - 1) * 256 + threadIdx.x;
+    if (tail && G.shift)
+        reset_rows<CodecMom>(cur, p, cd, wrapi(G.z0 - cd.dz, cd.nz), nullptr, 0, did, q, (gridDim.x - 1) * 256);
     if (q >= L3) return;
     float *D = p.dsh + cd.reg_off * 4;
     float sh[4] = {0.0f, 0.0f, 0.0f, 1.0f};
     unsigned char &mk = p.mark[cd.reg_off + q];
-    const int gz = B.org[2] + q / (L * L);
+    const int gz = G.org[2] + q / (L * L);
     if (mk && gz >= 0 && gz < cd.nz) {
         const long long *H = p.H + cd.reg_off * 3;
         long long h0 = 0, h1 = 0, h2 = 0;
@@ -1497,85 +1643,11 @@ __global__ void k_correct_mom(DevPtrs p, int resid_slot)
     for (int k = 0; k < 4; k++) D[k * (long long)L3 + q] = sh[k];
 }
 
-// ----------------------------------------------------------------- window
-// Sec. 2.5: below h_end the content and the body move up by dz rows.  With
-// the ring layout the move is the origin change z0 -> z0 - dz; the dz rows
-// that now form the bottom (the former top rows) restart at rest.
-// The step's record for the case's log ring, taken after the window test.
-struct StepRecord {
-    double v[kLogFields];
-};
-
-__device__ inline StepRecord window_trigger_case(const DevPtrs &p, int c)
-{
-    const CaseDev &cd = p.cases[c];
-    BodyDev &B = p.body[c];
-    // the test's operands in one round of loads (no short-circuit)
-    const int M = cd.M, dz = cd.dz, nz = cd.nz, err = B.err;
-    const double h_end = cd.h_end, rz = B.r[2];
-    const bool shift = (M > 0) & (err == 0) & (dz > 0) & (h_end > 0.0) & (rz < h_end);
-    B.shift_now = 0;
-    if (shift) {
-        B.r[2] = rz + (double)dz;
-        B.z0 = wrapi(B.z0 - dz, nz);
-        B.fo[0][2] += dz;   // the full-precision boxes move with the content
-        B.fo[1][2] += dz;
-        B.shift_now = 1;
-        B.shifts += 1;
-    }
-    StepRecord rec;
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-        rec.v[a] = B.r[a];
-        rec.v[12 + a] = B.v[a];
-        rec.v[15 + a] = B.w[a];
-        rec.v[18 + a] = B.F[a];
-        rec.v[21 + a] = B.T[a];
-        rec.v[24 + a] = B.Fp[a];
-    }
-#pragma unroll
-    for (int a = 0; a < 9; a++) rec.v[3 + a] = B.d[a];
-    rec.v[27] = B.resid;
-    rec.v[28] = B.steps;
-    rec.v[29] = B.shifts;
-    rec.v[30] = B.z0;
-    rec.v[31] = B.err;
-    return rec;
-}
-
-// Appends a record to the case's log ring.  Written last in its kernel: the
-// stores go through a plain double pointer, which the compiler must assume
-// may alias the body state, so no body field is read after them.
-__device__ inline void log_append(const DevPtrs &p, int c, const StepRecord &rec)
-{
-    BodyDev &B = p.body[c];
-    const unsigned int n = B.logged;
-    B.logged = n + 1;
-    double *dst = p.log + ((long long)c * kLogCap + n % kLogCap) * kLogFields;
-#pragma unroll
-    for (int k = 0; k < kLogFields; k++) dst[k] = rec.v[k];
-}
-
 __global__ void k_window_trigger(DevPtrs p, int n_cases)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= n_cases) return;
     const StepRecord rec = window_trigger_case(p, c);
-    log_append(p, c, rec);
-}
-
-// The end of one step and the start of the next in one launch, for steps
-// the library sequences itself (lbm_run, graph capture): the window test of
-// step t, then the body advance of step t + 1, then step t's record.  The
-// window reset that follows reads no field the advance writes (it uses the
-// ring origin and the full-precision box origins), so the result is that of
-// the separate kernels, bit for bit.
-__global__ void k_window_advance(DevPtrs p, int n_cases)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_cases) return;
-    const StepRecord rec = window_trigger_case(p, c);
-    body_advance_case(p, c);
     log_append(p, c, rec);
 }
 
@@ -1586,32 +1658,9 @@ __global__ void k_window_reset(typename CD::T *__restrict__ cur, DevPtrs p, int 
     const CaseDev &cd = p.cases[c];
     const BodyDev &B = p.body[c];
     if (!B.shift_now) return;
-    const int slab = cd.nx * cd.ny;
     // grid-strided: the launch stays small on the many steps without a shift
-    for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < cd.dz * slab; idx += gridDim.x * blockDim.x) {
-        const int zrow = idx / slab, rem = idx - zrow * slab;
-        int zc = zrow + B.z0;
-        if (zc >= cd.nz) zc -= cd.nz;
-        typename CD::T *dst = cur + cd.pop_off + (long long)zc * slab + rem;
-        if constexpr (std::is_same<CD, CodecMom>::value) {
-#pragma unroll
-            for (int k = 0; k < 10; k++) dst[(long long)k * cd.plane] = 0.0f;   // the rest state's moments
-        } else {
-            Unroll<0, Q>::run([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                dst[(long long)i * cd.plane] = CD::template enc<i>(0.0f);
-            });
-            if (cd.LB[0] > 0 && B.fvalid[cid]) {
-                const int slot = fine_slot(cd, B.fo[cid], rem % cd.nx, rem / cd.nx, zrow);
-                if (slot >= 0) {
-                    float *F = p.fine[cid] + cd.fine_off;
-                    const long long fplane = fine_plane(cd);
-#pragma unroll
-                    for (int i = 0; i < Q; i++) F[(long long)i * fplane + slot] = 0.0f;
-                }
-            }
-        }
-    }
+    reset_rows<CD>(cur, p, cd, B.z0, B.fo[cid], B.fvalid[cid], cid, blockIdx.x * blockDim.x + threadIdx.x,
+                   gridDim.x * blockDim.x);
 }
 
 // --------------------------------------------------------------- launchers
@@ -1711,25 +1760,26 @@ static hipError_t ibm_impl(const void *prev, void *cur, const DevPtrs &p, int n_
 }
 
 template <class CD>
-static hipError_t correct_impl(void *cur, const DevPtrs &p, int n_cases, int maxL3, int cur_id, int resid_slot,
+static hipError_t correct_impl(void *cur, const DevPtrs &p, int n_cases, int maxL3, int cur_id, int resid_slot, int tail,
                                hipStream_t s)
 {
-    const dim3 reg_grid((maxL3 + 255) / 256, n_cases);
-    hipLaunchKernelGGL(k_correct<CD>, reg_grid, dim3(256), 0, s, (typename CD::T *)cur, p, cur_id, resid_slot);
+    const dim3 grid(1 + (maxL3 + 255) / 256, n_cases);   // the first workgroup of a case ends its step
+    if constexpr (std::is_same<CD, CodecMom>::value)
+        hipLaunchKernelGGL(k_correct_mom, grid, dim3(256), 0, s, (float *)cur, p, cur_id, resid_slot, tail);
+    else
+        hipLaunchKernelGGL(k_correct<CD>, grid, dim3(256), 0, s, (typename CD::T *)cur, p, cur_id, resid_slot, tail);
     return hipGetLastError();
 }
 
 hipError_t launch_correct(int storage, void *cur, const DevPtrs &p, int n_cases, int Mtot, int maxL3, int cur_id,
-                          int resid_slot, hipStream_t s)
+                          int resid_slot, int tail, hipStream_t s)
 {
     if (Mtot == 0) return hipSuccess;
     switch (storage) {
-    case ST_MOM:
-        hipLaunchKernelGGL(k_correct_mom, dim3((maxL3 + 255) / 256, n_cases), dim3(256), 0, s, p, resid_slot);
-        return hipGetLastError();
-    case ST_F16: return correct_impl<CodecF16>(cur, p, n_cases, maxL3, cur_id, resid_slot, s);
-    case ST_BF16: return correct_impl<CodecBF16>(cur, p, n_cases, maxL3, cur_id, resid_slot, s);
-    default: return correct_impl<CodecF32>(cur, p, n_cases, maxL3, cur_id, resid_slot, s);
+    case ST_MOM: return correct_impl<CodecMom>(cur, p, n_cases, maxL3, cur_id, resid_slot, tail, s);
+    case ST_F16: return correct_impl<CodecF16>(cur, p, n_cases, maxL3, cur_id, resid_slot, tail, s);
+    case ST_BF16: return correct_impl<CodecBF16>(cur, p, n_cases, maxL3, cur_id, resid_slot, tail, s);
+    default: return correct_impl<CodecF32>(cur, p, n_cases, maxL3, cur_id, resid_slot, tail, s);
     }
 }
 
@@ -1761,13 +1811,9 @@ hipError_t launch_targets(const DevPtrs &p, int Mtot, float *out, hipStream_t s)
 }
 
 template <class CD>
-static hipError_t window_impl(void *cur, const DevPtrs &p, int n_cases, int max_slab, int cur_id, int advance,
-                              hipStream_t s)
+static hipError_t window_impl(void *cur, const DevPtrs &p, int n_cases, int max_slab, int cur_id, hipStream_t s)
 {
-    if (advance)
-        hipLaunchKernelGGL(k_window_advance, dim3((n_cases + 63) / 64), dim3(64), 0, s, p, n_cases);
-    else
-        hipLaunchKernelGGL(k_window_trigger, dim3((n_cases + 63) / 64), dim3(64), 0, s, p, n_cases);
+    hipLaunchKernelGGL(k_window_trigger, dim3((n_cases + 63) / 64), dim3(64), 0, s, p, n_cases);
     if (max_slab > 0) {
         // about 2048 workgroups in all, at least 8 per case
         const int per_case = std::max(8, std::min((max_slab + 255) / 256, 2048 / n_cases));
@@ -1777,14 +1823,13 @@ static hipError_t window_impl(void *cur, const DevPtrs &p, int n_cases, int max_
     return hipGetLastError();
 }
 
-hipError_t launch_window(int storage, void *cur, const DevPtrs &p, int n_cases, int max_slab, int cur_id, int advance,
-                         hipStream_t s)
+hipError_t launch_window(int storage, void *cur, const DevPtrs &p, int n_cases, int max_slab, int cur_id, hipStream_t s)
 {
     switch (storage) {
-    case ST_MOM: return window_impl<CodecMom>(cur, p, n_cases, max_slab, cur_id, advance, s);
-    case ST_F16: return window_impl<CodecF16>(cur, p, n_cases, max_slab, cur_id, advance, s);
-    case ST_BF16: return window_impl<CodecBF16>(cur, p, n_cases, max_slab, cur_id, advance, s);
-    default: return window_impl<CodecF32>(cur, p, n_cases, max_slab, cur_id, advance, s);
+    case ST_MOM: return window_impl<CodecMom>(cur, p, n_cases, max_slab, cur_id, s);
+    case ST_F16: return window_impl<CodecF16>(cur, p, n_cases, max_slab, cur_id, s);
+    case ST_BF16: return window_impl<CodecBF16>(cur, p, n_cases, max_slab, cur_id, s);
+    default: return window_impl<CodecF32>(cur, p, n_cases, max_slab, cur_id, s);
     }
 }
 
