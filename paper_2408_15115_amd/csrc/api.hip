@@ -344,7 +344,7 @@ std::string make_plan(const lbm_case *cases, const lbm_body *bodies, int n, cons
     P.off_cases = take(sizeof(CaseDev) * n);
     P.off_body = take(sizeof(BodyDev) * n);
     P.off_tiles = take(sizeof(Tile) * P.max_tiles);
-    P.off_counter = take(8 * sizeof(int));
+    P.off_counter = take(8 * kQueueStride * sizeof(int));
     P.off_mcase = take(sizeof(int) * M);
     P.off_xb = take(sizeof(double) * 3 * M);
     P.off_nb = take(sizeof(double) * 3 * M);

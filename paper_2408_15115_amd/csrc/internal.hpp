@@ -124,6 +124,8 @@ constexpr int kPart = 9;
 // Region fields: rho - 1, u (3), sigma xx yy zz xy xz yz (6).
 constexpr int kRegFields = 10;
 
+constexpr int kQueueStride = 32;   // a 128-byte line per counter
+
 struct DevPtrs {
     CaseDev *cases;
     StepGeometry *geo;
@@ -141,7 +143,7 @@ struct DevPtrs {
     float *reg;
     long long *H;    // kHBufs fixed-point immersed-force accumulators, hstride elements apart
     long long hstride;
-    int *counter;    // 8 work-queue counters of the persistent lattice schedule
+    int *counter;    // 8 work-queue counters of the persistent lattice schedule, kQueueStride apart
     MarkerTile *mtiles;
     float *feat;     // per-marker warm-start features (12)
     double *h0;      // per-marker plain start U - I[u*] (3)

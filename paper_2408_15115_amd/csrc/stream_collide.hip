@@ -92,7 +92,7 @@ __device__ __forceinline__ void stream_collide_tile(const typename CD::T *__rest
 // 2: persistent workgroups striding over the table; 3: persistent work
 // queue.  The queue is split in 8 contiguous segments with one counter each
 // (a single device-wide counter serializes every grab across the XCDs);
-// workgroup b starts on segment b mod 8, takes kQueueChunk tiles per grab and
+// workgroup b starts on segment b mod 8, takes `chunk` tiles per grab and
 // moves on to the other segments when its own is exhausted.  Counters only
 // grow, so every workgroup leaves the loop.  4: the same 8 counters, but
 // interleaved: counter g hands out chunks g, g + 8, g + 16, ... of the whole
@@ -101,47 +101,67 @@ __device__ __forceinline__ void stream_collide_tile(const typename CD::T *__rest
 // segments each XCD streams a case of its own, 8 times the plane streams).
 // (A queue of single wavefronts, without the barriers, was slower: four
 // times the grabs on the same counters.)
+// What bounds the queue is the counters: atomics of all XCDs on one address take
+// their turns (some 12 ns each).  So a workgroup's first chunk is its own
+// without a grab, the next grab is under way while a chunk is worked on, each
+// counter has a line of its own, and a workgroup whose part is exhausted looks
+// at all eight counters by loads before it grabs from another.  (With 1024
+// workgroups trying all eight counters at the end, a step took 105 us at least:
+// 97 x 46 x 101 in BF16, schedule 0: 15 us.)
 // One instantiation per schedule keeps the register allocation of the plain
 // schedules free of the loops.
 constexpr int kQueueChunk = 4;
+
+// First tile of the j-th chunk of a counter's part of the table, and the part's end.
+template <int SCHED>
+__device__ __forceinline__ int queue_tile(int grp, int j, int chunk, int ntiles)
+{
+    if constexpr (SCHED == 3) return grp * ((ntiles + 7) >> 3) + j * chunk;
+    else return (8 * j + grp) * chunk;
+}
+template <int SCHED>
+__device__ __forceinline__ int queue_end(int grp, int ntiles)
+{
+    if constexpr (SCHED == 3) return min(ntiles, (grp + 1) * ((ntiles + 7) >> 3));
+    else return ntiles;
+}
 
 template <class CD, int SCHED, int COLL = 0, bool KEEP = false>
 __global__ void __launch_bounds__(256) k_stream_collide(const typename CD::T *__restrict__ src,
                                                         typename CD::T *__restrict__ dst,
                                                         const CaseDev *__restrict__ cases, BodyDev *__restrict__ body,
                                                         const Tile *__restrict__ tiles, int ntiles,
-                                                        int *__restrict__ counter)
+                                                        int *__restrict__ counter, int chunk)
 {
-    if constexpr (SCHED == 3) {
-        __shared__ int s_t;
-        const int per = (ntiles + 7) >> 3;
-        for (int k = 0; k < 8; k++) {
-            const int grp = (blockIdx.x + k) & 7;
-            const int lo = grp * per, hi = min(ntiles, lo + per);
-            for (;;) {
-                if (threadIdx.x == 0) s_t = lo + kQueueChunk * atomicAdd(&counter[grp], 1);
-                __syncthreads();
-                const int t0 = __builtin_amdgcn_readfirstlane(s_t);
-                __syncthreads();
-                if (t0 >= hi) break;
-                const int t1 = min(t0 + kQueueChunk, hi);
-                for (int t = t0; t < t1; t++) stream_collide_tile<CD, COLL, KEEP>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
+    if constexpr (SCHED == 3 || SCHED == 4) {
+        __shared__ int s_next[2];
+        int grp = blockIdx.x & 7, j = blockIdx.x >> 3;
+        for (;;) {
+            const int t0 = queue_tile<SCHED>(grp, j, chunk, ntiles), end = queue_end<SCHED>(grp, ntiles);
+            int next = 0;
+            if (t0 < end) {
+                if (threadIdx.x == 0) next = atomicAdd(&counter[kQueueStride * grp], 1);
+                for (int t = t0; t < min(t0 + chunk, end); t++)
+                    stream_collide_tile<CD, COLL, KEEP>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
+            } else if (threadIdx.x < 64) {
+                // the next part, in this workgroup's order, that has chunks left
+                const int lane = threadIdx.x & 7, g = (blockIdx.x + lane) & 7;
+                const int n = __hip_atomic_load(&counter[kQueueStride * g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const bool left = queue_tile<SCHED>(g, ((int)gridDim.x - g + 7) / 8 + n, chunk, ntiles) <
+                                  queue_end<SCHED>(g, ntiles);
+                const int k = __ffsll((unsigned long long)(__ballot(left) & 0xff)) - 1;
+                grp = k < 0 ? -1 : (blockIdx.x + k) & 7;
+                if (k >= 0 && threadIdx.x == 0) next = atomicAdd(&counter[kQueueStride * grp], 1);
             }
-        }
-    } else if constexpr (SCHED == 4) {
-        __shared__ int s_j;
-        const int nchunks = (ntiles + kQueueChunk - 1) / kQueueChunk;
-        for (int k = 0; k < 8; k++) {
-            const int grp = (blockIdx.x + k) & 7;
-            for (;;) {
-                if (threadIdx.x == 0) s_j = atomicAdd(&counter[grp], 1);
-                __syncthreads();
-                const int chunk = 8 * __builtin_amdgcn_readfirstlane(s_j) + grp;
-                __syncthreads();
-                if (chunk >= nchunks) break;
-                const int t0 = chunk * kQueueChunk, t1 = min(t0 + kQueueChunk, ntiles);
-                for (int t = t0; t < t1; t++) stream_collide_tile<CD, COLL, KEEP>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                s_next[0] = grp;
+                s_next[1] = next;
             }
+            __syncthreads();
+            grp = __builtin_amdgcn_readfirstlane(s_next[0]);
+            if (grp < 0) break;
+            j = ((int)gridDim.x - grp + 7) / 8 + __builtin_amdgcn_readfirstlane(s_next[1]);
         }
     } else if constexpr (SCHED == 2) {
         for (int t = blockIdx.x; t < ntiles; t += gridDim.x) stream_collide_tile<CD, COLL, KEEP>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
@@ -154,7 +174,7 @@ __global__ void __launch_bounds__(256) k_stream_collide(const typename CD::T *__
 
 __global__ void k_reset_counter(int *counter)
 {
-    if (threadIdx.x < 8) counter[threadIdx.x] = 0;
+    if (threadIdx.x < 8) counter[kQueueStride * threadIdx.x] = 0;
 }
 
 // ------------------------------------------------------------ copy kernel
@@ -183,42 +203,44 @@ static hipError_t stream_collide_impl(const void *src, void *dst, const DevPtrs 
     using T = typename CD::T;
     if (collision == 1) {   // the comparison collision runs with the plain schedule only
         hipLaunchKernelGGL((k_stream_collide<CD, 0, 1>), dim3(ntiles), dim3(block), 0, s, (const T *)src, (T *)dst,
-                           p.cases, p.body, p.tiles, ntiles, p.counter);
+                           p.cases, p.body, p.tiles, ntiles, p.counter, 1);
         return hipGetLastError();
     }
     int grid = ntiles;
     if (schedule == 1) grid = (ntiles + 7) / 8 * 8;
     if (schedule >= 2) grid = persist_wgs > 0 ? persist_wgs : 2048;
+    // few tiles: smaller chunks, so that every workgroup still gets some
+    const int chunk = std::max(1, std::min(kQueueChunk, ntiles / (4 * std::max(grid, 1))));
     const T *a = (const T *)src;
     T *b = (T *)dst;
     switch (schedule) {
     case 1:
         hipLaunchKernelGGL((k_stream_collide<CD, 1>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles,
-                           ntiles, p.counter);
+                           ntiles, p.counter, chunk);
         break;
     case 2:
         hipLaunchKernelGGL((k_stream_collide<CD, 2>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles,
-                           ntiles, p.counter);
+                           ntiles, p.counter, chunk);
         break;
     case 3:
         hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, p.counter);
         hipLaunchKernelGGL((k_stream_collide<CD, 3>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles,
-                           ntiles, p.counter);
+                           ntiles, p.counter, chunk);
         break;
     case 4:
         hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, p.counter);
         hipLaunchKernelGGL((k_stream_collide<CD, 4>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles,
-                           ntiles, p.counter);
+                           ntiles, p.counter, chunk);
         break;
     default:
         if constexpr (std::is_same<CD, CodecF32>::value)
             if (keep) {
                 hipLaunchKernelGGL((k_stream_collide<CD, 0, 0, true>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body,
-                                   p.tiles, ntiles, p.counter);
+                                   p.tiles, ntiles, p.counter, chunk);
                 break;
             }
         hipLaunchKernelGGL((k_stream_collide<CD, 0>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles,
-                           ntiles, p.counter);
+                           ntiles, p.counter, chunk);
     }
     return hipGetLastError();
 }

@@ -77,3 +77,25 @@ def test_boxes_that_the_cache_holds_match_oracle(T, orc, lattice, nx, ny, nz):
     S.close()
     ref = np.moveaxis(collide(stream(C), tau), -1, 0)
     assert max_rel(gpu, ref) < 1e-5
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("schedule", [3, 4])
+def test_queue_takes_every_tile_once(T, storage, schedule):
+    """The work queue with fewer workgroups than counters, a few, and more than
+    tiles, in chunks of 1 to 4 tiles (the largest box has 1,425), on uneven
+    boxes: the fields of the plain schedule, bit for bit, over several steps."""
+    dims = [(48, 76, 100), (9, 8, 11), (33, 21, 40)]
+    cases = [W.make_case(*d, 0.6, W.BC_NOSLIP, W.BC_FREESLIP, 4) for d in dims]
+    rng = np.random.default_rng(7)
+    start = [W.D3Q27_W[:, None, None, None] * (1 + 0.02 * rng.standard_normal((27, *d[::-1]))) for d in dims]
+    out = []
+    for kw in [dict()] + [dict(schedule=schedule, persist_wgs=n) for n in (1, 5, 8, 61, 120, 700, 4000)]:
+        S = T.Solver(cases, None, storage=storage, **kw)
+        for c in range(3):
+            S.set_populations(start[c], c)
+        S.run(3)
+        out.append([S.populations(c) for c in range(3)])
+        S.close()
+        for c in range(3):
+            assert np.array_equal(out[-1][c], out[0][c]), (kw, c)
