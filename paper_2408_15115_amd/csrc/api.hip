@@ -721,31 +721,77 @@ static int32_t do_body_advance(lbm_ctx *ctx)
     return LBM_OK;
 }
 
-static int32_t do_lbm_step(lbm_ctx *ctx)
+// Which stream a step's two chains run on.
+enum StepOrder {
+    COUPLING_ASIDE,   // the lattice kernel on the context's stream, the coupling beside it on the second
+    LATTICE_ASIDE,    // the other way round
+    ONE_STREAM        // the coupling after the lattice kernel
+};
+
+static StepOrder separate_order(const lbm_ctx *ctx)
 {
+    return ctx->opt.serial_ibm ? ONE_STREAM : COUPLING_ASIDE;
+}
+
+// The order of steps that the library sequences itself, by the time of the
+// lattice kernel (estimated from its bytes).  Handing over between the streams
+// costs some 20 us on the longer chain's path, and the correction follows the
+// context's stream without it:
+//   - the coupling, some 100 us of short kernels, is the longer chain up to a
+//     lattice kernel of 75 us or so: then it stays on the context's stream.
+//     us a step with the coupling and with the lattice aside: 94 x 75 x 255 f16
+//     141 and 131, 71 x 126 x 273 bf16 161 and 153, four 92 x 42 x 84 of moments
+//     104 and 92; 150 x 131 x 211 of moments 142 and 154, 160 x 160 x 480 f32
+//     504 and 514.
+//   - a lattice kernel below 20 us is dearer beside than before the coupling:
+//     one stream takes 76 us at 48^3 f32, both forms with two 88; 68 x 98 x 120
+//     f16 121, 132 and 124.  In a captured graph every kernel beside another
+//     branch starts later, which counts for the many kernels of a warm start:
+//     there the line is at 45 us (228 x 92 x 77 bf16 195, 215 and 216; without a
+//     graph the host is behind and two streams win: 48 x 160 x 109 of moments
+//     173, 163 and 150).
+// Moment storage has a longest chain of planes that no small box goes below.
+static StepOrder run_order(const lbm_ctx *ctx, bool captured)
+{
+    if (ctx->opt.serial_ibm || !ctx->has_body) return separate_order(ctx);
+    const bool mom = ctx->opt.storage == LBM_MOM;
+    const double bytes = 2.0 * (double)ctx->plan.pop_elems * elem_bytes(ctx->opt.storage);
+    const double us = mom ? 15.0 + bytes / 5.0e6 : bytes / 5.3e6;
+    if (us < (captured && ctx->warm_mode ? 45.0 : mom ? 0.0 : 20.0)) return ONE_STREAM;
+    return us < 75.0 ? LATTICE_ASIDE : COUPLING_ASIDE;
+}
+
+static int32_t do_lbm_step(lbm_ctx *ctx, StepOrder order)
+{
+    const bool apart = ctx->has_body && order == LATTICE_ASIDE;
+    hipStream_t ls = apart ? ctx->side : ctx->stream;
     const int src = ctx->cur, dst = 1 - ctx->cur;
-    if (ctx->has_body) HIPCHK(ctx, hipEventRecord(ctx->fork, ctx->stream), "record fork event");
+    // (also ahead of a separate ibm_couple: the option may change in between)
+    if (ctx->has_body && (order != ONE_STREAM || ctx->opt.serial_ibm))
+        HIPCHK(ctx, hipEventRecord(ctx->fork, ctx->stream), "record fork event");
+    if (apart) HIPCHK(ctx, hipStreamWaitEvent(ctx->side, ctx->fork, 0), "side stream waits for the fork event");
     if (ctx->opt.storage == LBM_MOM)
         HIPCHK(ctx, launch_moment_step(ctx->pop[src], ctx->pop[dst], ctx->p, (int)ctx->plan.tiles.size(),
-                                       ctx->plan.cd[0].mom.cap, ctx->plan.keep, ctx->stream),
+                                       ctx->plan.cd[0].mom.cap, ctx->plan.keep, ls),
                "lbm_step");
     else if (ctx->plan.q == 19)
         HIPCHK(ctx,
                launch_stream_collide19(ctx->pop[src], ctx->pop[dst], ctx->p, (int)ctx->plan.tiles.size(),
-                                       ctx->opt.block, ctx->opt.collision, ctx->plan.keep, ctx->stream),
+                                       ctx->opt.block, ctx->opt.collision, ctx->plan.keep, ls),
                "lbm_step");
     else
         HIPCHK(ctx,
                launch_stream_collide(ctx->opt.storage, ctx->pop[src], ctx->pop[dst], ctx->p,
                                      (int)ctx->plan.tiles.size(), ctx->opt.block, ctx->opt.schedule,
-                                     ctx->opt.persist_wgs, ctx->opt.collision, ctx->plan.keep, ctx->stream),
+                                     ctx->opt.persist_wgs, ctx->opt.collision, ctx->plan.keep, ls),
                "lbm_step");
+    if (apart) HIPCHK(ctx, hipEventRecord(ctx->join, ctx->side), "record join event");
     if (ctx->plan.max_box > 0) {
         // the lattice kernel leaves the box cells to this step, which reads
         // only the buffer the lattice kernel reads: with the coupling beside
         // the lattice kernel it runs on the coupling's stream too, ahead of
         // the coupling (joined before the forced correction)
-        const bool beside = ctx->has_body && !ctx->opt.serial_ibm;
+        const bool beside = ctx->has_body && order == COUPLING_ASIDE;
         if (beside) HIPCHK(ctx, hipStreamWaitEvent(ctx->side, ctx->fork, 0), "side stream waits for the fork event");
         HIPCHK(ctx,
                launch_fine_step(ctx->opt.storage, ctx->pop[src], ctx->pop[dst], ctx->p, src, dst, ctx->n,
@@ -758,21 +804,19 @@ static int32_t do_lbm_step(lbm_ctx *ctx)
 }
 
 // tail: see launch_correct
-static int32_t do_ibm(lbm_ctx *ctx, int tail = 0)
+static int32_t do_ibm(lbm_ctx *ctx, StepOrder order, int tail = 0)
 {
     if (!ctx->has_body) return LBM_OK;
-    const bool serial = ctx->opt.serial_ibm != 0;
-    hipStream_t cs = serial ? ctx->stream : ctx->side;
-    if (!serial) HIPCHK(ctx, hipStreamWaitEvent(ctx->side, ctx->fork, 0), "side stream waits for the fork event");
+    const bool beside = order == COUPLING_ASIDE;
+    hipStream_t cs = beside ? ctx->side : ctx->stream;
+    if (beside) HIPCHK(ctx, hipStreamWaitEvent(ctx->side, ctx->fork, 0), "side stream waits for the fork event");
     HIPCHK(ctx,
            launch_ibm(ctx->opt.storage, ctx->pop[1 - ctx->cur], ctx->pop[ctx->cur], ctx->p, ctx->n, ctx->plan.Mtot,
                       (int)ctx->plan.mtiles.size(), ctx->plan.maxL3, ctx->opt.ibm_cycles, ctx->warm_mode, ctx->mlp_th16, ctx->mlp_cycles,
                       ctx->opt.ibm_diag, ctx->plan.force_surface, 1 - ctx->cur, cs),
            "ibm_couple");
-    if (!serial) {
-        HIPCHK(ctx, hipEventRecord(ctx->join, ctx->side), "record join event");
-        HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->join, 0), "stream waits for the coupling");
-    }
+    if (beside) HIPCHK(ctx, hipEventRecord(ctx->join, ctx->side), "record join event");
+    if (order != ONE_STREAM) HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->join, 0), "stream waits for the other chain");
     const int resid_slot =
         ibm_fused(ctx->warm_mode, ctx->opt.ibm_cycles) && !ctx->opt.ibm_diag ? ctx->opt.ibm_cycles - 1 : -1;
     HIPCHK(ctx, launch_correct(ctx->opt.storage, ctx->pop[ctx->cur], ctx->p, ctx->n, ctx->plan.Mtot, ctx->plan.maxL3,
@@ -801,14 +845,14 @@ int32_t lbm_step(lbm_ctx *ctx)
 {
     if (!ctx) return LBM_EINVAL;
     if (ctx->needs_ibm) return fail(ctx, LBM_ESTATE, "lbm_step twice without ibm_couple");
-    return do_lbm_step(ctx);
+    return do_lbm_step(ctx, separate_order(ctx));
 }
 
 int32_t ibm_couple(lbm_ctx *ctx)
 {
     if (!ctx) return LBM_EINVAL;
     if (ctx->has_body && !ctx->needs_ibm) return fail(ctx, LBM_ESTATE, "ibm_couple without a preceding lbm_step");
-    return do_ibm(ctx);
+    return do_ibm(ctx, separate_order(ctx));
 }
 
 int32_t window_shift(lbm_ctx *ctx)
@@ -820,13 +864,14 @@ int32_t window_shift(lbm_ctx *ctx)
 
 // nsteps whole steps in Table 1 order; the end of each step, and between two
 // of them the body advance, ride in the correction's launch.
-static int32_t run_steps(lbm_ctx *ctx, int nsteps)
+static int32_t run_steps(lbm_ctx *ctx, int nsteps, bool captured)
 {
     if (nsteps <= 0) return LBM_OK;
+    const StepOrder order = run_order(ctx, captured);
     int32_t r = do_body_advance(ctx);
     for (int s = 0; s < nsteps && r == LBM_OK; s++) {
-        if ((r = do_lbm_step(ctx))) return r;
-        r = do_ibm(ctx, s + 1 < nsteps ? 2 : 1);
+        if ((r = do_lbm_step(ctx, order))) return r;
+        r = do_ibm(ctx, order, s + 1 < nsteps ? 2 : 1);
     }
     return r;
 }
@@ -835,7 +880,7 @@ int32_t lbm_run(lbm_ctx *ctx, int32_t nsteps)
 {
     if (!ctx || nsteps < 0) return LBM_EINVAL;
     if (ctx->needs_ibm) return fail(ctx, LBM_ESTATE, "lbm_run between lbm_step and ibm_couple");
-    return run_steps(ctx, nsteps);
+    return run_steps(ctx, nsteps, false);
 }
 
 static void drop_graph(lbm_ctx *ctx);
@@ -892,7 +937,7 @@ int32_t lbm_graph_capture(lbm_ctx *ctx, int32_t steps)
     drop_graph(ctx);
     const int cur0 = ctx->cur;
     HIPCHK(ctx, hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-    int32_t r = run_steps(ctx, steps);
+    int32_t r = run_steps(ctx, steps, true);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(ctx->stream, &g);
     ctx->cur = cur0;

@@ -92,3 +92,44 @@ def test_step_end_equals_separate_calls(T, storage):
             assert np.array_equal(A.populations(c), B.populations(c)), c
             assert np.array_equal(A.log_read(c)[0], B.log_read(c)[0]), c
     assert A.body_state(0)["shifts"] == 1 and A.body_state(2, check=False)["err"] == 1 and A.body_state(3)["err"] == 0
+
+
+@pytest.mark.parametrize("storage,dims", [("f32", (24, 24, 40)), ("f32", (66, 68, 122)), ("f16", (96, 98, 110)),
+                                          ("mom", (24, 24, 40))])
+def test_step_orders_are_equal(T, storage, dims):
+    """lbm_run and a captured graph, which put the lattice kernel on the second
+    stream (moments, the larger boxes) or everything on one (the small box),
+    against the separate calls with the coupling on the second stream and
+    against the serial option, bit for bit, with and without a warm start."""
+    import torch
+    nx, ny, nz = dims
+    case = W.make_case(nx, ny, nz, 0.7, W.BC_FREESLIP, W.BC_FREESLIP, 5, 2e-5, h_ini=25.5, h_end=19.5 - 1e-6)
+    body = W.sphere_fibonacci_body(3.0, 200, 2.0, [nx / 2 - 0.2, ny / 2 + 0.3, 19.5])
+    stream = torch.cuda.Stream()
+    for warm in (0, T.LBM_WARM_PREVIOUS):
+        with torch.cuda.stream(stream):
+            runs = [T.Solver([case], [body], stream=stream, storage=storage, serial_ibm=k == 3) for k in range(4)]
+            for S in runs:
+                if warm:
+                    S.set_warm_start(warm, None, 3)
+                    S.set_ibm_gate(0, 1e-3)
+            for _ in range(6):
+                runs[0].body_advance()
+                runs[0].lbm_step()
+                runs[0].ibm_couple()
+                runs[0].window_shift()
+            runs[1].run(6)
+            runs[2].graph_capture(2)
+            for _ in range(3):
+                runs[2].graph_launch()
+            runs[3].run(6)
+            stream.synchronize()
+            a, pa = runs[0].body_state(), runs[0].populations()
+            assert a["shifts"] == 1
+            for S in runs[1:]:
+                b = S.body_state()
+                for k in a:
+                    assert np.array_equal(a[k], b[k]), (warm, k)
+                assert np.array_equal(pa, S.populations()), warm
+            for S in runs:
+                S.close()
