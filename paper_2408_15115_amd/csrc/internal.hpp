@@ -163,6 +163,23 @@ struct DevPtrs {
 // steps, shifts, z0, err), to a ring of kLogCap records.
 constexpr int kLogCap = 1024;
 constexpr int kLogFields = 32;
+// Host copy of a read (pinned): the case's record count and its first records.
+constexpr int kLogStage = 32;
+struct LogStage {
+    unsigned int logged, pad;
+    double rec[kLogStage * kLogFields];
+};
+// First unread record, and how many of at most room there are (the counts run
+// modulo 2^32; a reader more than kLogCap behind has lost the oldest).
+__host__ __device__ inline unsigned int log_start(unsigned int logged, unsigned int cur)
+{
+    return logged - cur > (unsigned int)kLogCap ? logged - (unsigned int)kLogCap : cur;
+}
+__host__ __device__ inline int log_available(unsigned int logged, unsigned int cur, int room)
+{
+    const unsigned int n = logged - log_start(logged, cur);
+    return n < (unsigned int)room ? (int)n : room;
+}
 
 // ---------------------------------------------------------------- launchers
 // keep: store the result with ordinary stores, not non-temporal ones (FP32;
@@ -215,6 +232,8 @@ hipError_t launch_correct(int storage, void *cur, const DevPtrs &p, int n_cases,
 inline bool ibm_fused(int warm_mode, int cycles) { return warm_mode == 0 && cycles <= kHBufs; }
 hipError_t launch_targets(const DevPtrs &p, int Mtot, float *out, hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, long long bytes, hipStream_t s);
+hipError_t launch_log_fetch(const DevPtrs &p, int c, unsigned int cur, int room, LogStage *out, hipStream_t s);
+
 // The window test and reset of Sec. 2.5 and the step's record.
 hipError_t launch_window(int storage, void *cur, const DevPtrs &p, int n_cases, int max_slab, int cur_id, hipStream_t s);
 

@@ -1651,6 +1651,18 @@ __global__ void k_window_trigger(DevPtrs p, int n_cases)
     log_append(p, c, rec);
 }
 
+// The unread records of case c (cur of them read so far, at most room wanted) to
+// pinned host memory, with the case's count.
+__global__ void __launch_bounds__(256) k_log_fetch(DevPtrs p, int c, unsigned int cur, int room, LogStage *__restrict__ out)
+{
+    const unsigned int logged = p.body[c].logged;
+    const int n = log_available(logged, cur, room);
+    const unsigned int at = log_start(logged, cur);
+    for (int i = threadIdx.x; i < min(n, kLogStage) * kLogFields; i += 256)
+        out->rec[i] = p.log[((long long)c * kLogCap + (at + i / kLogFields) % kLogCap) * kLogFields + i % kLogFields];
+    if (threadIdx.x == 0) out->logged = logged;
+}
+
 template <class CD>
 __global__ void k_window_reset(typename CD::T *__restrict__ cur, DevPtrs p, int cid)
 {
@@ -1807,6 +1819,12 @@ hipError_t launch_ibm(int storage, const void *prev, void *cur, const DevPtrs &p
 hipError_t launch_targets(const DevPtrs &p, int Mtot, float *out, hipStream_t s)
 {
     hipLaunchKernelGGL(k_targets, dim3((Mtot + 255) / 256), dim3(256), 0, s, p, Mtot, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_log_fetch(const DevPtrs &p, int c, unsigned int cur, int room, LogStage *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_log_fetch, dim3(1), dim3(256), 0, s, p, c, cur, room, out);
     return hipGetLastError();
 }
 
