@@ -180,6 +180,25 @@ void store_policy(Plan &P, int storage)
                                 : storage == LBM_F32 && bytes >= (40LL << 20) && bytes <= kCache;
 }
 
+// Whether FP32 kernels take the 64-bit form of a cell's place in a plane: from
+// 2^30 cells on they have to (a plane passes 4 GiB).  The other form (a scalar
+// base and a 32-bit offset) has half the vector instructions, but with less
+// between them the 27 loads of a cell leave closer together, and past some 9 GiB
+// of buffers the lattice kernel is the slower for it.  us a step, 64-bit and
+// 32-bit: 160 x 160 x 480 474 and 465, 300 x 140 x 500 829 and 820,
+// 224 x 224 x 672 1307 and 1289, 240 x 240 x 720 (9.0 GB) 1645 and 1642,
+// 250 x 250 x 760 (10.3 GB) 1936 and 1966, 256 x 256 x 768 1934 and 1957.  The
+// persistent schedules, whose fewer wavefronts have the same spacing at any
+// size, keep the 64-bit form: 160 x 160 x 480 by schedule 2 517 and 522, twelve
+// uneven boxes coupled by schedule 4 3603 and 3645.
+int wide_planes(const Plan &P, int storage)
+{
+    if (storage != LBM_F32) return 0;
+    for (const CaseDev &d : P.cd)
+        if (d.cells >= (1LL << 30)) return 2;
+    return 2 * P.pop_elems * elem_bytes(storage) > (9LL << 30);
+}
+
 // Marker order and tiles of one case: sort the markers along a Morton curve
 // of their body-frame positions (1.5-cell quantization), then cut the
 // sequence into tiles of at most kTileMarkers markers spanning at most
@@ -604,6 +623,7 @@ int32_t lbm_init(const lbm_case *cases, const lbm_body *bodies, int32_t n_cases,
     p.hstride = 3 * std::max<long long>(P.reg_cells, 1);
     p.mark = (unsigned char *)(a + P.off_mark);
     p.geo = (StepGeometry *)(a + P.off_geo);
+    p.wide = wide_planes(P, ctx->opt.storage);
     p.mark2 = (unsigned char *)(a + P.off_mark2);
     p.xmark = ctx->opt.storage == LBM_MOM ? (unsigned char *)(a + P.off_xmark) : nullptr;
     p.wt = (double *)(a + P.off_wt);

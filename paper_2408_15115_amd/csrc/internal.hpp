@@ -124,10 +124,25 @@ constexpr int kPart = 9;
 // Region fields: rho - 1, u (3), sigma xx yy zz xy xz yz (6).
 constexpr int kRegFields = 10;
 
+// Address of element `off` bytes into a plane that is the same for a whole
+// wavefront: a scalar base and a 32-bit lane offset, so that a load or a store
+// takes no vector arithmetic of its own.
+template <class T>
+__device__ __forceinline__ T *plane_at(T *base, unsigned int off)
+{
+    return (T *)((char *)base + off);
+}
+template <class T>
+__device__ __forceinline__ const T *plane_at(const T *base, unsigned int off)
+{
+    return (const T *)((const char *)base + off);
+}
+
 constexpr int kQueueStride = 32;   // a 128-byte line per counter
 
 struct DevPtrs {
     CaseDev *cases;
+    int wide;        // FP32 planes take 64-bit cell offsets: 1 in the lattice kernel, 2 everywhere (see wide_planes)
     StepGeometry *geo;
     BodyDev *body;
     Tile *tiles;

@@ -17,10 +17,17 @@ namespace turret {
 // form); periodic z wraps.  A no-slip wall may move in x at uw_lo / uw_hi:
 // bounce-back then adds the wall's momentum, 6 w_i rho0 (xi_i . u_w) with
 // rho0 = 1.  Physical row z sits in ring slot (z + z0) mod nz.
-template <class CD>
-__device__ inline void pull(const typename CD::T *__restrict__ src, long long plane, int nx, int ny, int nz,
-                            int z0, int bc_lo, int bc_hi, float uw_lo, float uw_hi, int x, int y, int z, float g[Q])
+// WIDE: FP32 planes past 4 GiB, whose cells need 64-bit offsets.
+// The rest addresses each plane by its scalar base and pulls the populations
+// that come from beyond a wall in a second pass, which most wavefronts skip: the
+// direction then is the same for all lanes.  With a direction per lane the
+// addresses were half of the kernel's vector instructions.
+template <class CD, bool WIDE>
+__device__ __forceinline__ void pull(const typename CD::T *__restrict__ src, long long plane, int nx, int ny, int nz,
+                                     int z0, int bc_lo, int bc_hi, float uw_lo, float uw_hi, int x, int y, int z,
+                                     float g[Q])
 {
+    using T = typename CD::T;
     const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
     const int ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
     int zc = z + z0;
@@ -29,35 +36,62 @@ __device__ inline void pull(const typename CD::T *__restrict__ src, long long pl
     const int zhi = zc == nz - 1 ? 0 : zc + 1;
     const bool wlo = (z == 0) && bc_lo != BC_PERIODIC;
     const bool whi = (z == nz - 1) && bc_hi != BC_PERIODIC;
-    const int rowc = zc * ny, rowlo = zlo * ny, rowhi = zhi * ny;
-    Unroll<0, Q>::run([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        int sx = cx(i) == 1 ? xm : (cx(i) == -1 ? xp : x);
-        int sy = cy(i) == 1 ? ym : (cy(i) == -1 ? yp : y);
-        int srow = cz(i) == 1 ? rowlo : (cz(i) == -1 ? rowhi : rowc);
-        int dir = i;
-        bool neg = false;
-        float add = 0.0f;
-        if constexpr (cz(i) != 0) {
-            const bool wall = cz(i) == 1 ? wlo : whi;
-            const int bc = cz(i) == 1 ? bc_lo : bc_hi;
-            if (wall) {
-                srow = rowc;
-                if (bc == BC_FREESLIP) {
-                    dir = mirror_z(i);
-                } else {
-                    dir = opposite(i);
-                    sx = x;
-                    sy = y;
-                    neg = bc == BC_PRESSURE;
-                    if constexpr (cx(i) != 0)
-                        if (bc == BC_NOSLIP) add = (float)(6.0 * wq(i) * cx(i)) * (cz(i) == 1 ? uw_lo : uw_hi);
+    if constexpr (WIDE) {
+        const int rowc = zc * ny, rowlo = zlo * ny, rowhi = zhi * ny;
+        Unroll<0, Q>::run([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            int sx = cx(i) == 1 ? xm : (cx(i) == -1 ? xp : x);
+            int sy = cy(i) == 1 ? ym : (cy(i) == -1 ? yp : y);
+            int srow = cz(i) == 1 ? rowlo : (cz(i) == -1 ? rowhi : rowc);
+            int dir = i;
+            bool neg = false;
+            float add = 0.0f;
+            if constexpr (cz(i) != 0) {
+                const bool wall = cz(i) == 1 ? wlo : whi;
+                const int bc = cz(i) == 1 ? bc_lo : bc_hi;
+                if (wall) {
+                    srow = rowc;
+                    if (bc == BC_FREESLIP) {
+                        dir = mirror_z(i);
+                    } else {
+                        dir = opposite(i);
+                        sx = x;
+                        sy = y;
+                        neg = bc == BC_PRESSURE;
+                        if constexpr (cx(i) != 0)
+                            if (bc == BC_NOSLIP) add = (float)(6.0 * wq(i) * cx(i)) * (cz(i) == 1 ? uw_lo : uw_hi);
+                    }
                 }
             }
-        }
-        const float v = CD::template dec<i>(src[(long long)dir * plane + (long long)((srow + sy) * nx + sx)]);
-        g[i] = (neg ? -v : v) + add;
-    });
+            const float v = CD::template dec<i>(src[(long long)dir * plane + (long long)((srow + sy) * nx + sx)]);
+            g[i] = (neg ? -v : v) + add;
+        });
+    } else {
+        const unsigned int ex = sizeof(T), ey = (unsigned int)nx * ex, ez = (unsigned int)ny * ey;
+        const unsigned int Z[3] = {zhi * ez, zc * ez, zlo * ez}, Y[3] = {yp * ey, y * ey, ym * ey},
+                           X[3] = {xp * ex, x * ex, xm * ex};   // by component of xi, -1 .. 1
+        Unroll<0, Q>::run([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            g[i] = CD::template dec<i>(*plane_at(src + i * plane, Z[cz(i) + 1] + Y[cy(i) + 1] + X[cx(i) + 1]));
+        });
+        if (!wlo && !whi) return;
+        Unroll<0, Q>::run([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            if constexpr (cz(i) != 0) {
+                if (!(cz(i) == 1 ? wlo : whi)) return;
+                const int bc = cz(i) == 1 ? bc_lo : bc_hi;
+                if (bc == BC_FREESLIP) {
+                    g[i] = CD::template dec<i>(*plane_at(src + mirror_z(i) * plane, Z[1] + Y[cy(i) + 1] + X[cx(i) + 1]));
+                    return;
+                }
+                const float v = CD::template dec<i>(*plane_at(src + opposite(i) * plane, Z[1] + Y[1] + X[1]));
+                float add = 0.0f;
+                if constexpr (cx(i) != 0)
+                    if (bc == BC_NOSLIP) add = (float)(6.0 * wq(i) * cx(i)) * (cz(i) == 1 ? uw_lo : uw_hi);
+                g[i] = (bc == BC_PRESSURE ? -v : v) + add;
+            }
+        });
+    }
 }
 
 }  // namespace turret

@@ -15,13 +15,15 @@ namespace turret {
 // next step: the stores carry the non-temporal hint (measured faster; the
 // same hint on the loads is not), unless the context's two FP32 buffers stay
 // in the memory-side cache (KEEP).
-template <class CD, bool KEEP>
+template <class CD, bool KEEP, bool WIDE>
 __device__ __forceinline__ void store_all(typename CD::T *__restrict__ dst, long long plane, int off, const float out[Q])
 {
     Unroll<0, Q>::run([&](auto I) {
         constexpr int i = decltype(I)::value;
-        if constexpr (KEEP) dst[(long long)i * plane + off] = CD::template enc<i>(out[i]);
-        else __builtin_nontemporal_store(CD::template enc<i>(out[i]), &dst[(long long)i * plane + off]);
+        typename CD::T *at = WIDE ? dst + i * plane + off
+                                  : plane_at(dst + i * plane, (unsigned int)off * (unsigned int)sizeof(typename CD::T));
+        if constexpr (KEEP) *at = CD::template enc<i>(out[i]);
+        else __builtin_nontemporal_store(CD::template enc<i>(out[i]), at);
     });
 }
 
@@ -31,7 +33,7 @@ __device__ __forceinline__ void store_all(typename CD::T *__restrict__ dst, long
 // flags non-finite density or |u| > 0.5 (bit 4) with one atomic per wave.
 // COLL 0: recursive-regularized collision (App. A); COLL 1: BGK for
 // comparison, f0 + (1 - 1/tau)(f - f0) with the raw off-equilibrium.
-template <class CD, int COLL, bool KEEP>
+template <class CD, int COLL, bool KEEP, bool WIDE>
 __device__ __forceinline__ void stream_collide_tile(const typename CD::T *__restrict__ src, typename CD::T *__restrict__ dst,
                                                     const CaseDev *__restrict__ cases, BodyDev *__restrict__ body, Tile tl,
                                                     int off)
@@ -62,7 +64,7 @@ __device__ __forceinline__ void stream_collide_tile(const typename CD::T *__rest
         }
     }
     float g[Q];
-    pull<CD>(src + cd.pop_off, cd.plane, nx, ny, nz, z0, cd.bc_lo, cd.bc_hi, cd.uw_lo, cd.uw_hi, x, y, z, g);
+    pull<CD, WIDE>(src + cd.pop_off, cd.plane, nx, ny, nz, z0, cd.bc_lo, cd.bc_hi, cd.uw_lo, cd.uw_hi, x, y, z, g);
     const Macro M = macro(raw_moments(g));
     const float u2 = M.u[0] * M.u[0] + M.u[1] * M.u[1] + M.u[2] * M.u[2];
     const bool bad = !(fabsf(M.r1) < 1.0f) || !(u2 < 0.25f);
@@ -83,7 +85,7 @@ __device__ __forceinline__ void stream_collide_tile(const typename CD::T *__rest
     if (in_box) return;
     int zc = z + z0;
     if (zc >= nz) zc -= nz;
-    store_all<CD, KEEP>(dst + cd.pop_off, cd.plane, (zc * ny + y) * nx + x, out);
+    store_all<CD, KEEP, WIDE>(dst + cd.pop_off, cd.plane, (zc * ny + y) * nx + x, out);
 }
 
 // SCHED 0: tile = workgroup; 1: XCD-grouped tiles (workgroups go
@@ -126,7 +128,7 @@ __device__ __forceinline__ int queue_end(int grp, int ntiles)
     else return ntiles;
 }
 
-template <class CD, int SCHED, int COLL = 0, bool KEEP = false>
+template <class CD, int SCHED, int COLL = 0, bool KEEP = false, bool WIDE = false>
 __global__ void __launch_bounds__(256) k_stream_collide(const typename CD::T *__restrict__ src,
                                                         typename CD::T *__restrict__ dst,
                                                         const CaseDev *__restrict__ cases, BodyDev *__restrict__ body,
@@ -142,7 +144,7 @@ __global__ void __launch_bounds__(256) k_stream_collide(const typename CD::T *__
             if (t0 < end) {
                 if (threadIdx.x == 0) next = atomicAdd(&counter[kQueueStride * grp], 1);
                 for (int t = t0; t < min(t0 + chunk, end); t++)
-                    stream_collide_tile<CD, COLL, KEEP>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
+                    stream_collide_tile<CD, COLL, KEEP, WIDE>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
             } else if (threadIdx.x < 64) {
                 // the next part, in this workgroup's order, that has chunks left
                 const int lane = threadIdx.x & 7, g = (blockIdx.x + lane) & 7;
@@ -164,11 +166,11 @@ __global__ void __launch_bounds__(256) k_stream_collide(const typename CD::T *__
             j = ((int)gridDim.x - grp + 7) / 8 + __builtin_amdgcn_readfirstlane(s_next[1]);
         }
     } else if constexpr (SCHED == 2) {
-        for (int t = blockIdx.x; t < ntiles; t += gridDim.x) stream_collide_tile<CD, COLL, KEEP>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
+        for (int t = blockIdx.x; t < ntiles; t += gridDim.x) stream_collide_tile<CD, COLL, KEEP, WIDE>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
     } else {
         int t = blockIdx.x;
         if constexpr (SCHED == 1) t = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-        if (t < ntiles) stream_collide_tile<CD, COLL, KEEP>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
+        if (t < ntiles) stream_collide_tile<CD, COLL, KEEP, WIDE>(src, dst, cases, body, tiles[t], (int)threadIdx.x);
     }
 }
 
@@ -201,11 +203,6 @@ static hipError_t stream_collide_impl(const void *src, void *dst, const DevPtrs 
                                       int schedule, int persist_wgs, int collision, int keep, hipStream_t s)
 {
     using T = typename CD::T;
-    if (collision == 1) {   // the comparison collision runs with the plain schedule only
-        hipLaunchKernelGGL((k_stream_collide<CD, 0, 1>), dim3(ntiles), dim3(block), 0, s, (const T *)src, (T *)dst,
-                           p.cases, p.body, p.tiles, ntiles, p.counter, 1);
-        return hipGetLastError();
-    }
     int grid = ntiles;
     if (schedule == 1) grid = (ntiles + 7) / 8 * 8;
     if (schedule >= 2) grid = persist_wgs > 0 ? persist_wgs : 2048;
@@ -213,34 +210,33 @@ static hipError_t stream_collide_impl(const void *src, void *dst, const DevPtrs 
     const int chunk = std::max(1, std::min(kQueueChunk, ntiles / (4 * std::max(grid, 1))));
     const T *a = (const T *)src;
     T *b = (T *)dst;
+    auto run = [&](auto sched, auto keep_form, auto wide) {
+        hipLaunchKernelGGL((k_stream_collide<CD, decltype(sched)::value, 0, decltype(keep_form)::value, decltype(wide)::value>),
+                           dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles, ntiles, p.counter, chunk);
+    };
+    constexpr std::integral_constant<bool, std::is_same<CD, CodecF32>::value> f32;   // (only FP32 has the 64-bit form)
+    if (collision == 1) {   // the comparison collision runs with the plain schedule only
+        auto bgk = [&](auto wide) {
+            hipLaunchKernelGGL((k_stream_collide<CD, 0, 1, false, decltype(wide)::value>), dim3(ntiles), dim3(block), 0, s, a,
+                               b, p.cases, p.body, p.tiles, ntiles, p.counter, 1);
+        };
+        if (f32 && p.wide) bgk(f32);
+        else bgk(std::false_type{});
+        return hipGetLastError();
+    }
+    if (schedule == 3 || schedule == 4) hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, p.counter);
     switch (schedule) {
     case 1:
-        hipLaunchKernelGGL((k_stream_collide<CD, 1>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles,
-                           ntiles, p.counter, chunk);
+        if (f32 && p.wide) run(std::integral_constant<int, 1>{}, std::false_type{}, f32);
+        else run(std::integral_constant<int, 1>{}, std::false_type{}, std::false_type{});
         break;
-    case 2:
-        hipLaunchKernelGGL((k_stream_collide<CD, 2>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles,
-                           ntiles, p.counter, chunk);
-        break;
-    case 3:
-        hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, p.counter);
-        hipLaunchKernelGGL((k_stream_collide<CD, 3>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles,
-                           ntiles, p.counter, chunk);
-        break;
-    case 4:
-        hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(64), 0, s, p.counter);
-        hipLaunchKernelGGL((k_stream_collide<CD, 4>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles,
-                           ntiles, p.counter, chunk);
-        break;
+    case 2: run(std::integral_constant<int, 2>{}, std::false_type{}, f32); break;
+    case 3: run(std::integral_constant<int, 3>{}, std::false_type{}, f32); break;
+    case 4: run(std::integral_constant<int, 4>{}, std::false_type{}, f32); break;
     default:
-        if constexpr (std::is_same<CD, CodecF32>::value)
-            if (keep) {
-                hipLaunchKernelGGL((k_stream_collide<CD, 0, 0, true>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body,
-                                   p.tiles, ntiles, p.counter, chunk);
-                break;
-            }
-        hipLaunchKernelGGL((k_stream_collide<CD, 0>), dim3(grid), dim3(block), 0, s, a, b, p.cases, p.body, p.tiles,
-                           ntiles, p.counter, chunk);
+        if (f32 && p.wide) run(std::integral_constant<int, 0>{}, std::false_type{}, f32);
+        else if (f32 && keep) run(std::integral_constant<int, 0>{}, f32, std::false_type{});
+        else run(std::integral_constant<int, 0>{}, std::false_type{}, std::false_type{});
     }
     return hipGetLastError();
 }

@@ -61,7 +61,7 @@ __device__ __forceinline__ int wrap(int v, int n)
 //      alone (om = 0), then out = geq + om (g - geq).
 // The moments on S and D, (a_1 + a_2) / (2 cs^6) and (a_1 - a_2) / (6 cs^6),
 // recombine on H_1 and H_2 as k1 = 18 a_1 + 9 a_2, k2 = 9 a_1 + 18 a_2.
-template <int COLL, bool KEEP>
+template <int COLL, bool KEEP, bool WIDE>
 __global__ void __launch_bounds__(256) k_stream_collide19(const float *__restrict__ src, float *__restrict__ dst,
                                                           const CaseDev *__restrict__ cases, BodyDev *__restrict__ body,
                                                           const Tile *__restrict__ tiles)
@@ -84,8 +84,16 @@ __global__ void __launch_bounds__(256) k_stream_collide19(const float *__restric
     const float *s = src + cd.pop_off;
     const long long plane = cd.plane;
     float g[N];
+    // scalar plane bases and 32-bit offsets, as in pull() (WIDE: planes past 4 GiB)
+    const unsigned int Z[3] = {(unsigned int)(rowhi * nx) * 4u, (unsigned int)(rowc * nx) * 4u, (unsigned int)(rowlo * nx) * 4u},
+                       Y[3] = {(unsigned int)(yp * nx) * 4u, (unsigned int)(y * nx) * 4u, (unsigned int)(ym * nx) * 4u},
+                       X[3] = {xp * 4u, x * 4u, xm * 4u};   // by component of xi, -1 .. 1
 #pragma unroll
     for (int i = 0; i < N; i++) {
+        if constexpr (!WIDE) {
+            g[i] = *plane_at(s + i * plane, Z[V.z[i] + 1] + Y[V.y[i] + 1] + X[V.x[i] + 1]);
+            continue;
+        }
         const int sx = V.x[i] == 1 ? xm : (V.x[i] == -1 ? xp : x);
         const int sy = V.y[i] == 1 ? ym : (V.y[i] == -1 ? yp : y);
         const int sr = V.z[i] == 1 ? rowlo : (V.z[i] == -1 ? rowhi : rowc);
@@ -172,19 +180,23 @@ __global__ void __launch_bounds__(256) k_stream_collide19(const float *__restric
         else
             out[i] = eq;
     }
-    float *d = dst + cd.pop_off + (rowc + y) * nx + x;
+    float *d = dst + cd.pop_off;
 #pragma unroll
     for (int i = 0; i < N; i++) {
-        if constexpr (KEEP) d[(long long)i * plane] = out[i];
-        else __builtin_nontemporal_store(out[i], &d[(long long)i * plane]);
+        float *at = WIDE ? d + i * plane + ((rowc + y) * nx + x) : plane_at(d + i * plane, Z[1] + Y[1] + X[1]);
+        if constexpr (KEEP) *at = out[i];
+        else __builtin_nontemporal_store(out[i], at);
     }
 }
 
 hipError_t launch_stream_collide19(const void *src, void *dst, const DevPtrs &p, int ntiles, int block,
                                    int collision, int keep, hipStream_t s)
 {
-    auto *kernel = collision == 1 ? (keep ? k_stream_collide19<1, true> : k_stream_collide19<1, false>)
-                                  : (keep ? k_stream_collide19<0, true> : k_stream_collide19<0, false>);
+    const bool wide = p.wide == 2;   // (keep goes with boxes far smaller)
+    auto *kernel = collision == 1 ? (wide ? k_stream_collide19<1, false, true>
+                                          : keep ? k_stream_collide19<1, true, false> : k_stream_collide19<1, false, false>)
+                                  : (wide ? k_stream_collide19<0, false, true>
+                                          : keep ? k_stream_collide19<0, true, false> : k_stream_collide19<0, false, false>);
     hipLaunchKernelGGL(kernel, dim3(ntiles), dim3(block), 0, s, (const float *)src, (float *)dst, p.cases, p.body, p.tiles);
     return hipGetLastError();
 }
