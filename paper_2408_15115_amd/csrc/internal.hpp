@@ -142,7 +142,7 @@ constexpr int kQueueStride = 32;   // a 128-byte line per counter
 
 struct DevPtrs {
     CaseDev *cases;
-    int wide;        // FP32 planes take 64-bit cell offsets: 1 in the lattice kernel, 2 everywhere (see wide_planes)
+    int wide;        // FP32 planes take 64-bit cell offsets in the lattice kernels: 1 by choice, 2 by need (see wide_planes)
     StepGeometry *geo;
     BodyDev *body;
     Tile *tiles;

@@ -323,7 +323,7 @@ __device__ __forceinline__ void gather_cell(const DevPtrs &p, const CaseDev &cd,
 
 // src: the buffer the lattice kernel read (moment storage: unused, the cells
 // pull from the expanded region).
-template <class CD, bool WIDE>
+template <class CD>
 __global__ void __launch_bounds__(256) EIGHT_WAVES k_region_gather(const typename CD::T *__restrict__ src, DevPtrs p, int sid)
 {
     __shared__ ScanList list;
@@ -350,7 +350,7 @@ __global__ void __launch_bounds__(256) EIGHT_WAVES k_region_gather(const typenam
                     return;
                 }
             }
-            pull<CD, WIDE>(src + cd.pop_off, cd.plane, cd.nx, cd.ny, cd.nz, B.z0, cd.bc_lo, cd.bc_hi, cd.uw_lo, cd.uw_hi, gx, gy,
+            pull<CD, true>(src + cd.pop_off, cd.plane, cd.nx, cd.ny, cd.nz, B.z0, cd.bc_lo, cd.bc_hi, cd.uw_lo, cd.uw_hi, gx, gy,
                      gz, g);
         }
     });
@@ -1700,11 +1700,7 @@ static hipError_t ibm_impl(const void *prev, void *cur, const DevPtrs &p, int n_
         hipLaunchKernelGGL(k_region_expand_mom, dim3((unsigned)((E3 + 255) / 256), n_cases), blk, 0, s,
                            (const T *)prev, p);
     }
-    if (std::is_same<CD, CodecF32>::value && p.wide == 2)
-        hipLaunchKernelGGL((k_region_gather<CD, std::is_same<CD, CodecF32>::value>), reg_grid, blk, 0, s, (const T *)prev, p,
-                           prev_id);
-    else
-        hipLaunchKernelGGL((k_region_gather<CD, false>), reg_grid, blk, 0, s, (const T *)prev, p, prev_id);
+    hipLaunchKernelGGL(k_region_gather<CD>, reg_grid, blk, 0, s, (const T *)prev, p, prev_id);
     // plain start with at most kHBufs cycles: each cycle's spread rides on
     // the pass before it (force + spread 1, update c + spread c + 1)
     static_assert(kHBufs == 4, "the launch below instantiates 1..4 accumulators");

@@ -129,7 +129,8 @@ __device__ __forceinline__ int queue_end(int grp, int ntiles)
 }
 
 template <class CD, int SCHED, int COLL = 0, bool KEEP = false, bool WIDE = false>
-__global__ void __launch_bounds__(256) k_stream_collide(const typename CD::T *__restrict__ src,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SCHED < 2 && COLL == 0 && !WIDE ? 8 : 4)))
+k_stream_collide(const typename CD::T *__restrict__ src,
                                                         typename CD::T *__restrict__ dst,
                                                         const CaseDev *__restrict__ cases, BodyDev *__restrict__ body,
                                                         const Tile *__restrict__ tiles, int ntiles,
