@@ -421,10 +421,10 @@ struct lbm_ctx {
     const _Float16 *mlp_th16 = nullptr;   // warm-start network (FP16 weights)
     int mlp_cycles = 0;
     // The coupling of a step reads only the body state and the buffer the
-    // lattice kernel reads, so it runs on `side` beside the lattice kernel:
-    // `fork` is recorded on `stream` just before the lattice kernel, `join`
-    // on `side` after the forcing cycles; the forced correction and
-    // everything after it wait for `join` on `stream`.
+    // lattice kernel reads, so one of the two runs on `side` beside the other
+    // (see StepOrder): `fork` is recorded on `stream` ahead of them, `join` on
+    // `side` after what ran there; the forced correction and everything after
+    // it wait for `join` on `stream`.
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
     LogStage *stage = nullptr;        // pinned, for lbm_log_read
