@@ -47,12 +47,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))
     float A[Q], out[Q];
     if constexpr (COLL == 1) {
         post_collision_coeffs(M, M.u, 0.0f, A);
-        hermite_to_populations<CD::kSplit>(A, out);
+        hermite_to_populations(A, out);
 #pragma unroll
         for (int i = 0; i < Q; i++) out[i] += om * (g[i] - out[i]);
     } else {
         post_collision_coeffs(M, M.u, om, A);
-        hermite_to_populations<CD::kSplit>(A, out);
+        hermite_to_populations(A, out);
     }
     int zc = z + z0;
     if (zc >= cd.nz) zc -= cd.nz;

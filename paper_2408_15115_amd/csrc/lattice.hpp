@@ -55,20 +55,14 @@ enum { BC_PERIODIC = 0, BC_FREESLIP = 1, BC_NOSLIP = 2, BC_PRESSURE = 3 };
 enum { ST_F32 = 0, ST_F16 = 1, ST_BF16 = 2, ST_MOM = 3 };
 
 // ------------------------------------------------------------------ codecs
-// kSplit: the collisions take outer_pair() in its split form.  For BF16: a code
-// that is off by one stays in a state for many steps, so its roundings stay those
-// that the store in integer arithmetic compiled to.  (The 27 instructions more
-// cost nothing: 160 x 160 x 480 with a body 320 us a step with and without.)
 struct CodecF32 {
     using T = float;
-    static constexpr bool kSplit = false;
     template <int I> __device__ static inline float dec(T v) { return v; }
     template <int I> __device__ static inline T enc(float g) { return g; }
 };
 
 struct CodecF16 {
     using T = _Float16;
-    static constexpr bool kSplit = false;
     template <int I> __device__ static inline float dec(T v)
     {
         return (float)v * (float)(1.0 / store_scale(I));
@@ -81,7 +75,6 @@ struct CodecF16 {
 
 struct CodecBF16 {
     using T = uint16_t;
-    static constexpr bool kSplit = true;
     template <int I> __device__ static inline float dec(T v)
     {
         return __uint_as_float((uint32_t)v << 16) * (float)(1.0 / store_scale(I));
@@ -247,25 +240,8 @@ __device__ inline void shift_coeffs(float rho, const float u[3], const float us[
     }
 }
 
-// lower = s - 3 a, upper = s + 3 a.  SPLIT: one FMA and a rounded product plus a
-// sum; else both as the compiler contracts them (FMAs).
-template <bool SPLIT>
-__device__ __forceinline__ void outer_pair(float s, float a, float &lower, float &upper)
-{
-    if constexpr (SPLIT) {
-#pragma clang fp contract(off)
-        lower = fmaf(-3.0f, a, s);
-        const float t = 3.0f * a;
-        upper = s + t;
-    } else {
-        lower = s - 3.0f * a;
-        upper = s + 3.0f * a;
-    }
-}
-
 // Hermite coefficients -> populations (deviation form): three 3-point passes
 // with e0 = 1, e1(-1,0,1) = (-3, 0, 3), e2(-1,0,1) = (3, -1.5, 3), then w_i.
-template <bool SPLIT = false>
 __device__ inline void hermite_to_populations(const float A[Q], float out[Q])
 {
     float T1[Q];   // [mx + 3 my + 9 kz]
@@ -273,8 +249,9 @@ __device__ inline void hermite_to_populations(const float A[Q], float out[Q])
     for (int k = 0; k < 9; k++) {
         float a0 = A[k], a1 = A[k + 9], a2 = A[k + 18];
         float s = a0 + 3.0f * a2;
-        outer_pair<SPLIT>(s, a1, T1[k], T1[k + 18]);
+        T1[k] = s - 3.0f * a1;
         T1[k + 9] = a0 - 1.5f * a2;
+        T1[k + 18] = s + 3.0f * a1;
     }
     float T2[Q];   // [mx + 3 ky + 9 kz]
 #pragma unroll
@@ -284,16 +261,18 @@ __device__ inline void hermite_to_populations(const float A[Q], float out[Q])
             int b = mx + 9 * kz;
             float a0 = T1[b], a1 = T1[b + 3], a2 = T1[b + 6];
             float s = a0 + 3.0f * a2;
-            outer_pair<SPLIT>(s, a1, T2[b], T2[b + 6]);
+            T2[b] = s - 3.0f * a1;
             T2[b + 3] = a0 - 1.5f * a2;
+            T2[b + 6] = s + 3.0f * a1;
         }
 #pragma unroll
     for (int r = 0; r < 9; r++) {      // r = ky + 3 kz
         int b = 3 * r;
         float a0 = T2[b], a1 = T2[b + 1], a2 = T2[b + 2];
         float s = a0 + 3.0f * a2;
-        outer_pair<SPLIT>(s, a1, out[b], out[b + 2]);
+        out[b] = s - 3.0f * a1;
         out[b + 1] = a0 - 1.5f * a2;
+        out[b + 2] = s + 3.0f * a1;
     }
 #pragma unroll
     for (int i = 0; i < Q; i++) out[i] *= (float)wq(i);

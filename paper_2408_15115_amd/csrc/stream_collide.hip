@@ -75,12 +75,12 @@ __device__ __forceinline__ void stream_collide_tile(const typename CD::T *__rest
     float A[Q], out[Q];
     if constexpr (COLL == 1) {
         post_collision_coeffs(M, M.u, 0.0f, A);   // equilibrium coefficients only
-        hermite_to_populations<CD::kSplit>(A, out);
+        hermite_to_populations(A, out);
 #pragma unroll
         for (int i = 0; i < Q; i++) out[i] += om * (g[i] - out[i]);
     } else {
         post_collision_coeffs(M, M.u, om, A);
-        hermite_to_populations<CD::kSplit>(A, out);
+        hermite_to_populations(A, out);
     }
     if (in_box) return;
     int zc = z + z0;
