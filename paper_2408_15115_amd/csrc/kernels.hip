@@ -27,6 +27,7 @@
 #include "pull.hpp"
 #include "mlp.hpp"
 #include "moments.hpp"
+#include "worklist.hpp"
 #include <type_traits>
 
 // Register budget of the coupling's kernels (the reason stands at the tile kernels).
@@ -177,35 +178,6 @@ struct CodecMom {
     using T = float;
 };
 
-// Work list of a region pass.  Only some of a region's cells take part in a
-// step (a sixth at the 256 x 256 x 768 ellipsoid), so a workgroup looks through
-// its cells, one per thread, and the ones that are wanted go to its first
-// threads: most wavefronts end at once, which counts where the rest wait for
-// slots that the lattice kernel frees.  More cells per workgroup pack them
-// closer but leave a small region too few workgroups (1024 cells: 119 us a step
-// instead of 101 in a 53 x 117 x 123 box, and nothing gained at the ellipsoid).
-// Returns the cell of thread k < n of the workgroup's 256 cells first .., -1 for
-// the others.  (At the ellipsoid 9 us a step on moment storage, 3 us on FP32,
-// against a thread per cell; nothing either way in small boxes.)
-struct ScanList {
-    unsigned char at[256];
-    int n[4];
-};
-
-__device__ inline int scan_cells(ScanList &l, int first, bool want)
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const unsigned long long m = __ballot(want);
-    if (lane == 0) l.n[w] = __popcll(m);
-    __syncthreads();
-    int at = 0;
-    for (int j = 0; j < w; j++) at += l.n[j];
-    if (want) l.at[at + __popcll(m & ((1ull << lane) - 1))] = (unsigned char)threadIdx.x;
-    __syncthreads();
-    const int n = l.n[0] + l.n[1] + l.n[2] + l.n[3];
-    return (int)threadIdx.x < n ? first + l.at[threadIdx.x] : -1;
-}
-
 // Moment storage, first pass of the region gather: the collided populations
 // (forcing shifts included) of the cells that the gather pulls from (marked by
 // k_markers in the region with a one-cell rim, edge E = L + 2), into rpop.  Rim
@@ -217,10 +189,9 @@ __global__ void __launch_bounds__(256) EIGHT_WAVES k_region_expand_mom(const flo
     const CaseDev cd = p.cases[c];
     const BodyView B = body_view(p.body[c]);
     const int E = cd.L + 2, E3 = E * E * E, first = blockIdx.x * 256;
-    if (cd.M == 0 || B.err != 0 || first >= E3) return;
+    if (cd.M == 0 || first >= E3) return;
     unsigned char *mk = p.xmark + cd.xreg_off;
-    const int i0 = first + threadIdx.x;
-    const int q = scan_cells(list, first, i0 < E3 && mk[i0]);
+    const int q = scan_cells(list, first, E3, B.err, [&](int i) { return mk[i]; });
     if (q < 0) return;
     mk[q] = 0;
     const int a = q % E, b = (q / E) % E, cc = q / (E * E);
@@ -331,9 +302,8 @@ __global__ void __launch_bounds__(256) EIGHT_WAVES k_region_gather(const typenam
     const CaseDev cd = p.cases[c];
     const BodyView B = body_view(p.body[c]);
     const int L3 = cd.L * cd.L * cd.L, first = blockIdx.x * 256;
-    if (cd.M == 0 || B.err != 0 || first >= L3) return;
-    const long long i0 = cd.reg_off + min(first + (int)threadIdx.x, L3 - 1);
-    const int q = scan_cells(list, first, (p.mark[i0] | p.mark2[i0]) != 0 && first + (int)threadIdx.x < L3);
+    if (cd.M == 0 || first >= L3) return;
+    const int q = scan_cells(list, first, L3, B.err, [&](int i) { return p.mark[cd.reg_off + i] | p.mark2[cd.reg_off + i]; });
     if (q < 0) return;
     gather_cell(p, cd, B.org, q, [&](int a, int b, int cc, int gz, float g[Q]) {
         if constexpr (std::is_same<CD, CodecMom>::value) {
@@ -1522,8 +1492,7 @@ __global__ void __launch_bounds__(256) k_correct(typename CD::T *__restrict__ cu
     }
     if (first >= L3) return;
     unsigned char *mk = p.mark + cd.reg_off;
-    const int i0 = first + threadIdx.x;
-    const int q = scan_cells(list, first, i0 < L3 && mk[i0]);
+    const int q = scan_cells(list, first, L3, 0, [&](int i) { return mk[i]; });   // (err is settled: both streams have joined)
     if (q < 0) return;
     mk[q] = 0;
     const int a = q % L, b = (q / L) % L, cc = q / (L * L);
