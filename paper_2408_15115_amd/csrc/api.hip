@@ -790,8 +790,7 @@ static int32_t do_lbm_step(lbm_ctx *ctx, StepOrder order)
     const bool apart = ctx->has_body && order == LATTICE_ASIDE;
     hipStream_t ls = apart ? ctx->side : ctx->stream;
     const int src = ctx->cur, dst = 1 - ctx->cur;
-    // (also ahead of a separate ibm_couple: the option may change in between)
-    if (ctx->has_body && (order != ONE_STREAM || ctx->opt.serial_ibm))
+    if (ctx->has_body && order != ONE_STREAM)
         HIPCHK(ctx, hipEventRecord(ctx->fork, ctx->stream), "record fork event");
     if (apart) HIPCHK(ctx, hipStreamWaitEvent(ctx->side, ctx->fork, 0), "side stream waits for the fork event");
     if (ctx->opt.storage == LBM_MOM)
@@ -921,10 +920,11 @@ int32_t lbm_set_schedule(lbm_ctx *ctx, const lbm_options *opt)
     if (ctx->plan.q == 19 && opt->schedule != 0) return fail(ctx, LBM_EINVAL, "the D3Q19 lattice runs with schedule 0");
     if (ctx->opt.storage == LBM_MOM && (opt->schedule != 0 || opt->collision != 0))
         return fail(ctx, LBM_EINVAL, "moment storage runs with schedule 0 and collision 0");
+    // before anything is stored: ibm_couple follows the stream order of its lbm_step
+    if (ctx->needs_ibm) return fail(ctx, LBM_ESTATE, "lbm_set_schedule between lbm_step and ibm_couple");
     if (opt->serial_ibm != ctx->opt.serial_ibm || opt->collision != ctx->opt.collision) drop_graph(ctx);
     ctx->opt.serial_ibm = opt->serial_ibm;
     ctx->opt.collision = opt->collision;
-    if (ctx->needs_ibm) return fail(ctx, LBM_ESTATE, "lbm_set_schedule between lbm_step and ibm_couple");
     const int block = opt->block ? opt->block : 256;
     if (ctx->opt.storage == LBM_MOM)
         build_moment_tiles(ctx->plan);
