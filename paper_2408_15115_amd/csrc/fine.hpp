@@ -81,7 +81,7 @@ __device__ inline void pull_fine(const typename CD::T *__restrict__ src, const f
                     ky = by;
                     neg = bc == BC_PRESSURE;
                     if constexpr (cx(i) != 0)
-                        if (bc == BC_NOSLIP) add = (float)(6.0 * wq(i) * cx(i)) * (cz(i) == 1 ? cd.uw_lo : cd.uw_hi);
+                        if (bc == BC_NOSLIP) add = wall_momentum<i>(cz(i) == 1 ? cd.uw_lo : cd.uw_hi);
                 }
             }
         }

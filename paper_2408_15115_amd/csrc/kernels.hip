@@ -239,7 +239,7 @@ __device__ inline void pull_region(const DevPtrs &p, const CaseDev &cd, int a, i
             }
             const float v = R[opposite(i) * p.xstride + cell];
             if (bc == BC_PRESSURE) g[i] = -v;
-            else if constexpr (cx(i) != 0) g[i] = v + (float)(6.0 * wq(i) * cx(i)) * (cz(i) == 1 ? cd.uw_lo : cd.uw_hi);
+            else if constexpr (cx(i) != 0) g[i] = v + wall_momentum<i>(cz(i) == 1 ? cd.uw_lo : cd.uw_hi);
             else g[i] = v;
         }
     });

@@ -52,6 +52,17 @@ __host__ __device__ constexpr int scale_exp(int i) { return 14 + 2 * (cx(i) * cx
 __host__ __device__ constexpr double store_scale(int i) { return (double)(1ull << scale_exp(i)); }
 
 enum { BC_PERIODIC = 0, BC_FREESLIP = 1, BC_NOSLIP = 2, BC_PRESSURE = 3 };
+
+// What a no-slip wall moving in x at uw adds to population i, 6 w_i rho0
+// (xi_i . u_w) with rho0 = 1.  The product is rounded, never contracted into the
+// sum it goes to, so that all forms of the pull give the same bits.
+template <int I>
+__device__ __forceinline__ float wall_momentum(float uw)
+{
+#pragma clang fp contract(off)
+    return (float)(6.0 * wq(I) * cx(I)) * uw;
+}
+
 enum { ST_F32 = 0, ST_F16 = 1, ST_BF16 = 2, ST_MOM = 3 };
 
 // ------------------------------------------------------------------ codecs

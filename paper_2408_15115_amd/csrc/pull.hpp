@@ -61,7 +61,7 @@ __device__ __forceinline__ void pull(const typename CD::T *__restrict__ src, lon
                         sy = y;
                         neg = bc == BC_PRESSURE;
                         if constexpr (cx(i) != 0)
-                            if (bc == BC_NOSLIP) add = (float)(6.0 * wq(i) * cx(i)) * (cz(i) == 1 ? uw_lo : uw_hi);
+                            if (bc == BC_NOSLIP) add = wall_momentum<i>(cz(i) == 1 ? uw_lo : uw_hi);
                     }
                 }
             }
@@ -98,7 +98,7 @@ __device__ __forceinline__ void pull(const typename CD::T *__restrict__ src, lon
                 constexpr int i = decltype(I)::value;
                 if constexpr (cz(i) == decltype(S)::value) {
                     if (bc == BC_PRESSURE) g[i] = -g[i];
-                    else if constexpr (cx(i) != 0) g[i] += (float)(6.0 * wq(i) * cx(i)) * uw;
+                    else if constexpr (cx(i) != 0) g[i] += wall_momentum<i>(uw);
                 }
             });
         };
