@@ -1343,7 +1343,7 @@ static size_t mlp_layout(int max_batch, size_t off[8])
         o = align256(o + std::max<size_t>(bytes, 1));
         return at;
     };
-    const size_t P = kMlpParams, parts = std::min<size_t>((size_t)max_batch, kMlpParts);
+    const size_t P = kMlpParams, parts = (size_t)train_blocks(max_batch);
     off[0] = take(4 * P);           // th32
     off[1] = take(2 * P);           // th16
     off[2] = take(4 * P);           // m

@@ -293,7 +293,7 @@ __global__ void __launch_bounds__(256) k_mlp_warm_start(const _Float16 *__restri
 // ------------------------------------------------------------- training
 // Forward, backward and the weight gradients in one pass, on
 // v_mfma_f32_16x16x4_f32: FP32 operands (the FP16 weights widened) and FP32
-// accumulation throughout.  A workgroup of 4 waves takes 64 samples at a time.
+// accumulation throughout.  A workgroup of 4 waves takes kTrainSamples samples at a time.
 // Each wave runs 16 of them, the columns of every product, through the layers
 // and back in registers: with step e of a 16-wide chunk taking input 4 g + e
 // in lanes 16 g .. 16 g + 15, the rows a lane holds of one product are the
@@ -310,7 +310,6 @@ __global__ void __launch_bounds__(256) k_mlp_warm_start(const _Float16 *__restri
 // one thread per sample or parameter through HBM scratch, and takes 17 us so
 // (13 for this kernel).
 typedef float row4_t __attribute__((ext_vector_type(4)));
-constexpr int kTrainSamples = 64;            // per workgroup and round
 constexpr int kTrainPitch = kTrainSamples + 4;   // floats per LDS row: 16-byte aligned, no bank conflicts
 
 struct TrainLds {
@@ -598,10 +597,6 @@ hipError_t launch_mlp_warm_start(const _Float16 *th16, const DevPtrs &p, int Mto
     hipLaunchKernelGGL(k_mlp_warm_start, infer_grid(Mtot), dim3(256), 0, s, th16, p, Mtot);
     return hipGetLastError();
 }
-
-// Workgroups of the training pass: one per 64 samples up to one per CU, which
-// then take several rounds.
-static int train_blocks(int n) { return std::min((n + kTrainSamples - 1) / kTrainSamples, kMlpParts); }
 
 hipError_t launch_mlp_grad(const _Float16 *th16, const float *X, const float *Tg, int n, const MlpScratch &sc,
                            float *grad, float *loss, hipStream_t s)

@@ -25,10 +25,19 @@ constexpr int kMlpParts = 256;                 // most partial gradients of a ba
 // s_k.
 constexpr int kFeatH0 = 0, kFeatHPrev = 3, kFeatDH = 6, kFeatDH0 = 9, kFeatNormal = 12, kFeatArea = 15;
 
-// Training scratch.
+// Workgroups of the training pass over n samples: one per kTrainSamples up to one
+// per CU, which then take several rounds.
+constexpr int kTrainSamples = 64;
+inline int train_blocks(int n)
+{
+    const int all = (n + kTrainSamples - 1) / kTrainSamples;
+    return all < kMlpParts ? all : kMlpParts;
+}
+
+// Training scratch, for the workgroups of the largest batch.
 struct MlpScratch {
-    float *part;        // partial gradients [kMlpParts][kMlpParams]
-    float *loss_part;   // partial losses [kMlpParts]
+    float *part;        // partial gradients [train_blocks][kMlpParams]
+    float *loss_part;   // partial losses [train_blocks]
 };
 
 struct DevPtrs;
