@@ -310,6 +310,8 @@ __global__ void __launch_bounds__(256) k_mlp_warm_start(const _Float16 *__restri
 // one thread per sample or parameter through HBM scratch, and takes 17 us so
 // (13 for this kernel).
 typedef float row4_t __attribute__((ext_vector_type(4)));
+// A caller's samples: rows at any float (the load is one instruction either way).
+typedef float sample4_t __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int kTrainPitch = kTrainSamples + 4;   // floats per LDS row: 16-byte aligned, no bank conflicts
 
 struct TrainLds {
@@ -413,7 +415,7 @@ __global__ void __launch_bounds__(256) k_mlp_train(const _Float16 *__restrict__ 
         row4_t x = {0.0f, 0.0f, 0.0f, 0.0f}, dy = x;
         float tg[kMlpOut] = {};
         if (on) {
-            x = *reinterpret_cast<const row4_t *>(X + (long long)s * kMlpIn + 4 * g);
+            x = *reinterpret_cast<const sample4_t *>(X + (long long)s * kMlpIn + 4 * g);
             if (g == 0)
 #pragma unroll
                 for (int e = 0; e < kMlpOut; e++) tg[e] = Tg[(long long)s * kMlpOut + e];
