@@ -843,7 +843,7 @@ static int32_t do_ibm(lbm_ctx *ctx, StepOrder order, int tail = 0)
     const int resid_slot =
         ibm_fused(ctx->warm_mode, ctx->opt.ibm_cycles) && !ctx->opt.ibm_diag ? ctx->opt.ibm_cycles - 1 : -1;
     HIPCHK(ctx, launch_correct(ctx->opt.storage, ctx->pop[ctx->cur], ctx->p, ctx->n, ctx->plan.Mtot, ctx->plan.maxL3,
-                               ctx->cur, resid_slot, tail, ctx->stream),
+                               ctx->plan.max_slab, ctx->cur, resid_slot, tail, ctx->stream),
            "forced correction");
     ctx->needs_ibm = false;
     return LBM_OK;

@@ -240,8 +240,8 @@ hipError_t launch_ibm(int storage, const void *prev, void *cur, const DevPtrs &p
 // resid and resid_hist[resid_slot].
 // tail 1: the correction's launch also ends the step (the window test and reset
 // and the step's record); 2: and advances the bodies for the next step.
-hipError_t launch_correct(int storage, void *cur, const DevPtrs &p, int n_cases, int Mtot, int maxL3, int cur_id,
-                          int resid_slot, int tail, hipStream_t s);
+hipError_t launch_correct(int storage, void *cur, const DevPtrs &p, int n_cases, int Mtot, int maxL3, int max_slab,
+                          int cur_id, int resid_slot, int tail, hipStream_t s);
 // Whether the plain forcing sequence runs fused (each spread in the preceding
 // interpolation pass); it then leaves its residual to the correction.
 inline bool ibm_fused(int warm_mode, int cycles) { return warm_mode == 0 && cycles <= kHBufs; }

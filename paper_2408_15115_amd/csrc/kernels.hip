@@ -1741,10 +1741,16 @@ static hipError_t ibm_impl(const void *prev, void *cur, const DevPtrs &p, int n_
 }
 
 template <class CD>
-static hipError_t correct_impl(void *cur, const DevPtrs &p, int n_cases, int maxL3, int cur_id, int resid_slot, int tail,
-                               hipStream_t s)
+static hipError_t correct_impl(void *cur, const DevPtrs &p, int n_cases, int maxL3, int max_slab, int cur_id,
+                               int resid_slot, int tail, hipStream_t s)
 {
-    const dim3 grid(1 + (maxL3 + 255) / 256, n_cases);   // the first workgroup of a case ends its step
+    // The first workgroup of a case ends its step; the others correct the region
+    // and, on a step whose window moves, reset the rows.  A small body's region
+    // has too few workgroups for the rows of a wide box (230 x 230 with a body of
+    // 8 cells, 64 rows: 340 us more on such a step, 43 with one workgroup per CU,
+    // no less with 1024; 160 x 160 with one of 16 in FP16: 75 and 16).
+    const int reset = tail == TAIL_NONE ? 0 : std::min((max_slab + 255) / 256, std::max(8, 256 / n_cases));
+    const dim3 grid(1 + std::max((maxL3 + 255) / 256, reset), n_cases);
     if constexpr (std::is_same<CD, CodecMom>::value)
         hipLaunchKernelGGL(k_correct_mom, grid, dim3(256), 0, s, (float *)cur, p, cur_id, resid_slot, tail);
     else
@@ -1752,15 +1758,15 @@ static hipError_t correct_impl(void *cur, const DevPtrs &p, int n_cases, int max
     return hipGetLastError();
 }
 
-hipError_t launch_correct(int storage, void *cur, const DevPtrs &p, int n_cases, int Mtot, int maxL3, int cur_id,
-                          int resid_slot, int tail, hipStream_t s)
+hipError_t launch_correct(int storage, void *cur, const DevPtrs &p, int n_cases, int Mtot, int maxL3, int max_slab,
+                          int cur_id, int resid_slot, int tail, hipStream_t s)
 {
     if (Mtot == 0) return hipSuccess;
     switch (storage) {
-    case ST_MOM: return correct_impl<CodecMom>(cur, p, n_cases, maxL3, cur_id, resid_slot, tail, s);
-    case ST_F16: return correct_impl<CodecF16>(cur, p, n_cases, maxL3, cur_id, resid_slot, tail, s);
-    case ST_BF16: return correct_impl<CodecBF16>(cur, p, n_cases, maxL3, cur_id, resid_slot, tail, s);
-    default: return correct_impl<CodecF32>(cur, p, n_cases, maxL3, cur_id, resid_slot, tail, s);
+    case ST_MOM: return correct_impl<CodecMom>(cur, p, n_cases, maxL3, max_slab, cur_id, resid_slot, tail, s);
+    case ST_F16: return correct_impl<CodecF16>(cur, p, n_cases, maxL3, max_slab, cur_id, resid_slot, tail, s);
+    case ST_BF16: return correct_impl<CodecBF16>(cur, p, n_cases, maxL3, max_slab, cur_id, resid_slot, tail, s);
+    default: return correct_impl<CodecF32>(cur, p, n_cases, maxL3, max_slab, cur_id, resid_slot, tail, s);
     }
 }
 
