@@ -182,21 +182,29 @@ void store_policy(Plan &P, int storage)
 
 // Whether FP32 kernels take the 64-bit form of a cell's place in a plane: from
 // 2^30 cells on they have to (a plane passes 4 GiB).  The other form (a scalar
-// base and a 32-bit offset) has half the vector instructions, but with less
-// between them the 27 loads of a cell leave closer together, and past some 9 GiB
-// of buffers the lattice kernel is the slower for it.  us a step, 64-bit and
-// 32-bit: 160 x 160 x 480 474 and 465, 300 x 140 x 500 829 and 820,
-// 224 x 224 x 672 1307 and 1289, 240 x 240 x 720 (9.0 GB) 1645 and 1642,
-// 250 x 250 x 760 (10.3 GB) 1936 and 1966, 256 x 256 x 768 1934 and 1957.  The
-// persistent schedules, whose fewer wavefronts have the same spacing at any
-// size, keep the 64-bit form: 160 x 160 x 480 by schedule 2 517 and 522, twelve
-// uneven boxes coupled by schedule 4 3603 and 3645.
+// base and a 32-bit offset) has half the vector instructions, which is the better
+// one except for two ranges of a context's buffers (both together; lattice kernel
+// alone, us a step, 64-bit and 32-bit; FP32 fluid stepped from a random flow):
+//   - 28 to 40 MB, where the two buffers just pass the L2s: 52^3 (29 MB) 9.5 and
+//     9.7, 40 x 40 x 90 9.1 and 9.6, 55^3 9.5 and 10.9, 75 x 92 x 27 (38 MB) 9.7
+//     and 10.9, 58^3 (40 MB) 9.9 and 11.3; 50^3 (26 MB) 9.4 and 8.9, 48^3 8.4 and
+//     8.0.  From 40 MB on the stores are ordinary ones (store_policy), which the
+//     32-bit form alone has;
+//   - past 9 GiB, one box or many: 256 x 256 x 768 1944 and 1969, 300 x 300 x 700
+//     2533 and 2563, 200 x 200 x 1200 1903 and 1903, twelve of 160^3 (10.6 GB) 1992
+//     and 2027, 64 of 90 x 90 x 100 2021 and 2035, 48 of 128 x 128 x 64 2067 and
+//     2064; below, 224 x 224 x 672 (7.3 GB) 1335 and 1301, eight of 160 x 160 x 64
+//     524 and 507, 160 x 160 x 480 484 and 470.  With a body 256 x 256 x 768 2028
+//     and 2045, 200 x 200 x 1200 1985 and 2013.
+// The persistent schedules keep the 64-bit form: 160 x 160 x 480 by schedule 2 517
+// and 522, twelve uneven boxes coupled by schedule 4 3603 and 3645.
 int wide_planes(const Plan &P, int storage)
 {
     if (storage != LBM_F32) return 0;
     for (const CaseDev &d : P.cd)
         if (d.cells >= (1LL << 30)) return 2;
-    return 2 * P.pop_elems * elem_bytes(storage) > (9LL << 30);
+    const long long bytes = 2 * P.pop_elems * elem_bytes(storage);
+    return bytes > (9LL << 30) || (bytes >= (28LL << 20) && bytes < (40LL << 20));
 }
 
 // Marker order and tiles of one case: sort the markers along a Morton curve

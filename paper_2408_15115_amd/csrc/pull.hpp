@@ -17,13 +17,15 @@ namespace turret {
 // form); periodic z wraps.  A no-slip wall may move in x at uw_lo / uw_hi:
 // bounce-back then adds the wall's momentum, 6 w_i rho0 (xi_i . u_w) with
 // rho0 = 1.  Physical row z sits in ring slot (z + z0) mod nz.
-// WIDE: FP32 planes past 4 GiB, whose cells need 64-bit offsets.
+// WIDE: 64-bit cell offsets, which FP32 planes past 4 GiB need; also taken where
+// they are the faster form (wide_planes), by the persistent FP32 schedules and by
+// the region gather.
 // The rest addresses each plane by its scalar base: with a direction per lane, as
 // the rules of the walls need it, the addresses were half of the kernel's vector
 // instructions.  Cells at a wall then load the populations that come from beyond
 // it over the first ones, all of a side's in the same round and before anything
-// waits for the first (one after the other they cost low boxes 9 %: 78 x 199 x 13
-// in BF16 5.5 us a step against 5.1).
+// waits for the first (one after the other they cost low boxes up to 14 %: 78 x 199
+// x 13 in BF16 9.8 us a step against 8.4).
 template <class CD, bool WIDE>
 __device__ __forceinline__ void pull(const typename CD::T *__restrict__ src, long long plane, int nx, int ny, int nz,
                                      int z0, int bc_lo, int bc_hi, float uw_lo, float uw_hi, int x, int y, int z,
