@@ -1463,10 +1463,10 @@ int32_t mlp_train_step(lbm_mlp *m, const float *dev_x, const float *dev_t, int32
 {
     if (!m || !dev_x || !dev_t || n < 1 || n > m->max_batch)
         return m ? mlp_fail(m, LBM_EINVAL, "mlp_train_step: bad arguments or n > max_batch") : LBM_EINVAL;
-    m->step += 1;
-    hipError_t e = launch_mlp_train_step(m->th32, m->th16, m->m, m->v, dev_x, dev_t, n, m->sc, lr, m->step,
+    hipError_t e = launch_mlp_train_step(m->th32, m->th16, m->m, m->v, dev_x, dev_t, n, m->sc, lr, m->step + 1,
                                          dev_loss ? dev_loss : m->loss, m->stream);
     if (e != hipSuccess) return mlp_fail(m, LBM_EHIP, std::string("mlp_train_step: ") + hipGetErrorString(e));
+    m->step += 1;
     return LBM_OK;
 }
 

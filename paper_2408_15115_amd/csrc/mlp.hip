@@ -615,6 +615,8 @@ hipError_t launch_mlp_train_step(float *th32, _Float16 *th16, float *m, float *v
     const int nb = train_blocks(n);
     const AdamState A{th32, m, v, th16, lr, 1.0f - powf(0.9f, (float)step), 1.0f - powf(0.999f, (float)step)};
     hipLaunchKernelGGL(k_mlp_train, dim3(nb), dim3(256), 0, s, th16, X, Tg, n, sc);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;   // the parameters stay as they are
     hipLaunchKernelGGL(k_mlp_reduce<true>, dim3((kMlpParams + 63) / 64), dim3(1024), 0, s, nb, sc, nullptr, loss, A);
     return hipGetLastError();
 }
