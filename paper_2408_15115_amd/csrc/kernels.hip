@@ -1799,8 +1799,10 @@ hipError_t launch_targets(const DevPtrs &p, int Mtot, float *out, hipStream_t s)
 
 hipError_t launch_log_fetch(const DevPtrs &p, int c, unsigned int cur, int room, LogStage *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_log_fetch, dim3(1), dim3(256), 0, s, p, c, cur, room, out);
-    return hipGetLastError();
+    // the launch's own status: a read does not answer for errors of earlier calls
+    DevPtrs ptrs = p;
+    void *args[] = {&ptrs, &c, &cur, &room, &out};
+    return hipLaunchKernel((const void *)k_log_fetch, dim3(1), dim3(256), args, 0, s);
 }
 
 template <class CD>

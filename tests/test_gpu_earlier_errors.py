@@ -20,6 +20,21 @@ def leave_an_error():
     hip.hipGetLastError()
 
 
+def test_step_log_is_read(leave_an_error):
+    import torch
+    from paper_2408_15115_amd import turret as T
+    case = W.make_case(24, 24, 40, 0.7, W.BC_FREESLIP, W.BC_FREESLIP, 4, 2e-5)
+    S = T.Solver([case], [W.sphere_fibonacci_body(3.0, 150, 2.0, [11.5, 11.5, 20.0])])
+    S.run(40)
+    torch.cuda.synchronize()
+    assert leave_an_error() != 0
+    first, lost = S.log_read(0, 3)
+    assert first[:, 28].tolist() == [1, 2, 3] and lost == 0
+    rest, _ = S.log_read(0)
+    assert rest[:, 28].tolist() == list(range(4, 41))
+    S.close()
+
+
 def test_training_step_that_fails_leaves_the_parameters(leave_an_error):
     import torch
     from paper_2408_15115_amd import turret as T
