@@ -169,27 +169,35 @@ void build_moment_tiles(Plan &P)
 //     not whole 64-cell wavefronts: the hint writes the lines that two rows
 //     share in parts.  160 x 160 x 480: 308 and 244 us; 250 x 250 x 760: 1233
 //     and 1008; 256 x 256 x 400: 489 and 501.
+constexpr long long kMemorySideCache = 256LL << 20;
 void store_policy(Plan &P, int storage)
 {
-    constexpr long long kCache = 256LL << 20;
     const long long bytes = 2 * P.pop_elems * elem_bytes(storage);
     // moment storage: whichever holds for more of the context's cells
     long long whole = 0, ragged = 0;
     for (const CaseDev &d : P.cd) (d.nx % 64 != 0 ? ragged : whole) += d.cells;
-    P.keep = storage == LBM_MOM ? bytes >= kCache / 4 && (bytes <= kCache || ragged > whole)
-                                : storage == LBM_F32 && bytes >= (40LL << 20) && bytes <= kCache;
+    P.keep = storage == LBM_MOM ? bytes >= kMemorySideCache / 4 && (bytes <= kMemorySideCache || ragged > whole)
+                                : storage == LBM_F32 && bytes >= (40LL << 20) && bytes <= kMemorySideCache;
 }
 
 // Whether FP32 kernels take the 64-bit form of a cell's place in a plane: from
 // 2^30 cells on they have to (a plane passes 4 GiB).  The other form (a scalar
 // base and a 32-bit offset) has half the vector instructions, which is the better
-// one except for two ranges of a context's buffers (both together; lattice kernel
+// one except for three ranges of a context's buffers (both together; lattice kernel
 // alone, us a step, 64-bit and 32-bit; FP32 fluid stepped from a random flow):
 //   - 28 to 40 MB, where the two buffers just pass the L2s: 52^3 (29 MB) 9.5 and
 //     9.7, 40 x 40 x 90 9.1 and 9.6, 55^3 9.5 and 10.9, 75 x 92 x 27 (38 MB) 9.7
 //     and 10.9, 58^3 (40 MB) 9.9 and 11.3; 50^3 (26 MB) 9.4 and 8.9, 48^3 8.4 and
 //     8.0.  From 40 MB on the stores are ordinary ones (store_policy), which the
 //     32-bit form alone has;
+//   - with a body, from there (past the memory-side cache) to 1.5 GB: the 32-bit
+//     form, whose loads leave closer together, slows the coupling beside it, which
+//     is of like length.  us a coupled step: 108 x 298 x 75 161 and 169, 129 x 129 x
+//     300 227 and 238, 285 x 239 x 61 231 and 243, 97 x 151 x 350 230 and 239,
+//     176 x 185 x 180 250 and 254, eight uneven boxes (903 MB) 222 and 235; 65 x 229 x
+//     401 the other way, 320 and 316.  Above, it goes by a box's sizes: 160 x 160 x
+//     480 509 and 502, 250^3 647 and 633, 200^3 346 and 346, 151 x 201 x 418 556 and
+//     568, 256^3 670 and 678;
 //   - past 9 GiB, one box or many: 256 x 256 x 768 1944 and 1969, 300 x 300 x 700
 //     2533 and 2563, 200 x 200 x 1200 1903 and 1903, twelve of 160^3 (10.6 GB) 1992
 //     and 2027, 64 of 90 x 90 x 100 2021 and 2035, 48 of 128 x 128 x 64 2067 and
@@ -204,7 +212,8 @@ int wide_planes(const Plan &P, int storage)
     for (const CaseDev &d : P.cd)
         if (d.cells >= (1LL << 30)) return 2;
     const long long bytes = 2 * P.pop_elems * elem_bytes(storage);
-    return bytes > (9LL << 30) || (bytes >= (28LL << 20) && bytes < (40LL << 20));
+    return bytes > (9LL << 30) || (bytes >= (28LL << 20) && bytes < (40LL << 20)) ||
+           (P.Mtot > 0 && bytes > kMemorySideCache && bytes < (3LL << 29));
 }
 
 // Marker order and tiles of one case: sort the markers along a Morton curve

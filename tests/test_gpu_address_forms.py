@@ -1,6 +1,6 @@
 """The two forms of a cell's place in its plane (scalar base and 32-bit offset, or
 64-bit offsets) give the same bits: FP32 boxes on both sides of the sizes where
-the plain schedule changes form (28 and 40 MB of buffers), against the persistent
+the plain schedule changes form (28 and 40 MB of buffers; with a body 256 MB), against the persistent
 schedule, which always takes the 64-bit one; and the D3Q19 kernel in a box of
 2^30 cells, whose planes pass 4 GiB, against a box that it repeats along z."""
 import numpy as np
@@ -35,6 +35,20 @@ def test_forms_agree(T, nx, ny, nz, bc):
         assert S.body_state(0, check=False)["err"] == 0
         S.close()
     assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+
+
+def test_forms_agree_beside_a_body(T):
+    # 110^3: past the memory-side cache, the 64-bit form for its body's sake
+    case = W.make_case(110, 111, 110, 0.7, W.BC_FREESLIP, W.BC_FREESLIP, 8, 2e-5)
+    body = W.sphere_fibonacci_body(5.0, 400, 2.0, [54.3, 55.1, 54.8])
+    out = []
+    for opts in ({}, {"schedule": 4}):
+        S = T.Solver([case], [body], **opts)
+        S.run(6)
+        out.append((S.populations(), S.body_state()))
+        S.close()
+    assert np.array_equal(out[0][0], out[1][0])
+    assert all(np.array_equal(out[0][1][k], out[1][1][k]) for k in out[0][1])
 
 
 @pytest.mark.parametrize("collision", [0, 1])
