@@ -190,14 +190,17 @@ void store_policy(Plan &P, int storage)
 //     and 10.9, 58^3 (40 MB) 9.9 and 11.3; 50^3 (26 MB) 9.4 and 8.9, 48^3 8.4 and
 //     8.0.  From 40 MB on the stores are ordinary ones (store_policy), which the
 //     32-bit form alone has;
-//   - with a body, from there (past the memory-side cache) to 1.5 GB: the 32-bit
-//     form, whose loads leave closer together, slows the coupling beside it, which
-//     is of like length.  us a coupled step: 108 x 298 x 75 161 and 169, 129 x 129 x
-//     300 227 and 238, 285 x 239 x 61 231 and 243, 97 x 151 x 350 230 and 239,
-//     176 x 185 x 180 250 and 254, eight uneven boxes (903 MB) 222 and 235; 65 x 229 x
-//     401 the other way, 320 and 316.  Above, it goes by a box's sizes: 160 x 160 x
-//     480 509 and 502, 250^3 647 and 633, 200^3 346 and 346, 151 x 201 x 418 556 and
-//     568, 256^3 670 and 678;
+//   - with a body, past the memory-side cache, where the coupling beside it is of
+//     like length: the 32-bit form, whose loads leave closer together, slows it. us a
+//     coupled step, up to 1.75 GiB: 108 x 298 x 75 161 and 169, 129 x 129 x 300 227
+//     and 238, 285 x 239 x 61 231 and 243, 97 x 151 x 350 230 and 239, 176 x 185 x
+//     180 250 and 254, 200^3 352 and 350 (with a body of 60 cells 385 and 400),
+//     eight uneven boxes (903 MB) 222 and 235; 65 x 229 x 401 the other way, 320 and
+//     316.  Above, it goes by a box's sizes: 160 x 160 x 480 511 and 502, 250^3 651
+//     and 640, 151 x 201 x 418 561 and 572, 300^3 1102 and 1116.  The longer chains (a
+//     warm start, or cycles in passes of their own) are slowed there too: starts from
+//     the previous force at 210 x 205 x 238 454 and 479, 160 x 160 x 480 513 and 540,
+//     220 x 180 x 300 559 and 619, 240 x 240 x 720 1691 and 1718; 250^3 658 and 645;
 //   - past 9 GiB, one box or many: 256 x 256 x 768 1944 and 1969, 300 x 300 x 700
 //     2533 and 2563, 200 x 200 x 1200 1903 and 1903, twelve of 160^3 (10.6 GB) 1992
 //     and 2027, 64 of 90 x 90 x 100 2021 and 2035, 48 of 128 x 128 x 64 2067 and
@@ -206,14 +209,14 @@ void store_policy(Plan &P, int storage)
 //     and 2045, 200 x 200 x 1200 1985 and 2013.
 // The persistent schedules keep the 64-bit form: 160 x 160 x 480 by schedule 2 517
 // and 522, twelve uneven boxes coupled by schedule 4 3603 and 3645.
-int wide_planes(const Plan &P, int storage)
+int wide_planes(const Plan &P, int storage, bool fused)
 {
     if (storage != LBM_F32) return 0;
     for (const CaseDev &d : P.cd)
         if (d.cells >= (1LL << 30)) return 2;
     const long long bytes = 2 * P.pop_elems * elem_bytes(storage);
     return bytes > (9LL << 30) || (bytes >= (28LL << 20) && bytes < (40LL << 20)) ||
-           (P.Mtot > 0 && bytes > kMemorySideCache && bytes < (3LL << 29));
+           (P.Mtot > 0 && bytes > kMemorySideCache && (!fused || bytes < (7LL << 28)));
 }
 
 // Marker order and tiles of one case: sort the markers along a Morton curve
@@ -640,7 +643,7 @@ int32_t lbm_init(const lbm_case *cases, const lbm_body *bodies, int32_t n_cases,
     p.hstride = 3 * std::max<long long>(P.reg_cells, 1);
     p.mark = (unsigned char *)(a + P.off_mark);
     p.geo = (StepGeometry *)(a + P.off_geo);
-    p.wide = wide_planes(P, ctx->opt.storage);
+    p.wide = wide_planes(P, ctx->opt.storage, ibm_fused(ctx->warm_mode, ctx->opt.ibm_cycles));
     p.mark2 = (unsigned char *)(a + P.off_mark2);
     p.xmark = ctx->opt.storage == LBM_MOM ? (unsigned char *)(a + P.off_xmark) : nullptr;
     p.wt = (double *)(a + P.off_wt);
@@ -1498,6 +1501,7 @@ int32_t lbm_set_warm_start(lbm_ctx *ctx, int32_t mode, const lbm_mlp *m, int32_t
     ctx->warm_mode = mode;
     ctx->mlp_th16 = mode == LBM_WARM_MLP ? m->th16 : nullptr;
     ctx->mlp_cycles = mode == LBM_WARM_NONE ? 0 : cycles;
+    ctx->p.wide = wide_planes(ctx->plan, ctx->opt.storage, ibm_fused(mode, ctx->opt.ibm_cycles));
     return LBM_OK;
 }
 

@@ -1,6 +1,7 @@
 """The two forms of a cell's place in its plane (scalar base and 32-bit offset, or
 64-bit offsets) give the same bits: FP32 boxes on both sides of the sizes where
-the plain schedule changes form (28 and 40 MB of buffers; with a body 256 MB), against the persistent
+the plain schedule changes form (28 and 40 MB of buffers; with a body
+256 MB and 1.75 GiB), against the persistent
 schedule, which always takes the 64-bit one; and the D3Q19 kernel in a box of
 2^30 cells, whose planes pass 4 GiB, against a box that it repeats along z."""
 import numpy as np
@@ -37,18 +38,24 @@ def test_forms_agree(T, nx, ny, nz, bc):
     assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
 
 
-def test_forms_agree_beside_a_body(T):
-    # 110^3: past the memory-side cache, the 64-bit form for its body's sake
-    case = W.make_case(110, 111, 110, 0.7, W.BC_FREESLIP, W.BC_FREESLIP, 8, 2e-5)
-    body = W.sphere_fibonacci_body(5.0, 400, 2.0, [54.3, 55.1, 54.8])
-    out = []
+@pytest.mark.parametrize("n,warm", [(110, 0), (215, 0), (215, 1)])
+def test_forms_agree_beside_a_body(T, n, warm):
+    # 110: past the memory-side cache, the 64-bit form for the body's sake; 215
+    # (past 1.75 GiB): for a warm start alone
+    import torch
+    case = W.make_case(n, n + 1, n, 0.7, W.BC_FREESLIP, W.BC_FREESLIP, 8, 2e-5)
+    body = W.sphere_fibonacci_body(5.0, 400, 2.0, [n / 2 - 0.7, n / 2 + 0.1, n / 2 - 0.2])
+    runs = []
     for opts in ({}, {"schedule": 4}):
         S = T.Solver([case], [body], **opts)
+        S.set_warm_start(warm, None, 2)
         S.run(6)
-        out.append((S.populations(), S.body_state()))
-        S.close()
-    assert np.array_equal(out[0][0], out[1][0])
-    assert all(np.array_equal(out[0][1][k], out[1][1][k]) for k in out[0][1])
+        runs.append((S, S.body_state(), next(b for b in S.bufs[:2] if b.data_ptr() == S.current_buffer()).view(torch.int32)))
+    (A, a, fa), (B, b, fb) = runs
+    assert all(np.array_equal(a[k], b[k]) for k in a)
+    assert a["err"] == 0 and torch.equal(fa, fb)
+    A.close()
+    B.close()
 
 
 @pytest.mark.parametrize("collision", [0, 1])
