@@ -162,6 +162,10 @@ void build_moment_tiles(Plan &P)
 //     written back from the L2s when the kernel ends: FP32 48^3: 8.7 and 9.7,
 //     56^3 (38 MB): 9.8 and 11.6, 60^3 (47 MB): 13.0 and 12.3; D3Q19 56^3
 //     (27 MB): 7.7 and 8.9, 64^3 (40 MB): 9.0 and 9.0, 72^3: 14.4 and 12.7.
+//     The gain is there while a box stays in the cache: three boxes of 203 MB in
+//     turn, two steps each, 56 and 52, a box that other work has pushed out before
+//     its three or four steps up to 4 % slower than with the hint (D3Q19 219 x 216
+//     x 33: 44 and 46 a step).
 //     With 2-byte elements the two are within 5 % up to there, either way, so
 //     that form keeps the hint; moment storage below 64 MB too (64^3: 13.8 and
 //     14.4; 112^3: 41 and 36);
